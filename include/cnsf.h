@@ -180,6 +180,12 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * Lattices of at most 2^21 cells replay a HIP graph of 32 updates, captured on
  * first use, when n >= 64 (the results are those of single launches); while the
  * lattice's stream is itself being captured, the updates are plain launches.
+ * Periodic lattices for which it is faster (most of 96^3 and more) advance four
+ * updates at a time, two per pass over memory, with the same results bit for
+ * bit, when n >= 4 (5 from an odd level).  The first such call allocates a
+ * workspace, kept until cnsf_destroy: the array's size up to 2 GiB, an eighth
+ * of the array beyond, at most an eighth of the free device memory; without it
+ * (or after cnsf_set_launch) the lattice stays on single updates.
  * CNSF_E_DEVICE if a launch fails. */
 int cnsf_step(cnsf_lattice* lat, int64_t n);
 
@@ -189,7 +195,7 @@ int cnsf_step(cnsf_lattice* lat, int64_t n);
  * lattice by 1 + steps.  The same update runs at different speeds in
  * different physical allocations of the array, and an allocation keeps its
  * speed; an allocation policy probes candidate arrays with this and keeps the
- * fastest.  Errors as cnsf_step. */
+ * fastest.  Always single updates.  Errors as cnsf_step. */
 int cnsf_probe_update_ms(cnsf_lattice* lat, int32_t steps, double* ms);
 
 /* Q_k = sum_i f_{k,i} (the zeroth moment, Section 2.2) of the current time
@@ -269,7 +275,8 @@ int cnsf_hbm_copy(void* dst, const void* src, size_t bytes, void* stream);
  * that many blocks striding over the tiles; xcd_remap gives each of the 8 XCDs
  * one contiguous span of tiles.  block: 64..256 in steps of 64 (the kernels are
  * compiled for at most 256).  Defaults are the shapes measured fastest on
- * MI355X for the lattice's storage type. */
+ * MI355X for the lattice's storage type.  After this call cnsf_step makes
+ * single updates only, in this shape. */
 int cnsf_set_launch(cnsf_lattice* lat, int32_t block, int32_t tile, int32_t grid, int32_t xcd_remap);
 int cnsf_get_launch(const cnsf_lattice* lat, int32_t* block, int32_t* tile, int32_t* grid, int32_t* xcd_remap);
 

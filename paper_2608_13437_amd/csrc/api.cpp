@@ -2,6 +2,7 @@
 // lattice lifecycle, state set/readout, stepping, diagnostics, checkpoints.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -238,6 +239,11 @@ struct cnsf_lattice {
   // small lattices: GRAPH_STEPS updates captured once and replayed (launch-bound otherwise)
   hipStream_t gstream = nullptr;         // capture stream
   hipGraphExec_t gexec = nullptr;
+  // two updates per pass: workspace and cut of the lattice, decided at the first call that can use them
+  void* pair_ws = nullptr;
+  PairPlan pair;
+  bool pair_decided = false;
+  bool own_launch = false;               // the caller chose the launch shape of the update
 };
 
 namespace {
@@ -259,6 +265,33 @@ hipError_t launch_steps(cnsf_lattice* L, int64_t n, hipStream_t s, int& parity) 
     parity ^= 1;
   }
   return hipSuccess;
+}
+
+// Updates of one pass forward and one back (pair.hip).
+constexpr int64_t PAIR_STEPS = 4;
+// Workspace of the paired passes: a second array for lattices up to 2 GiB, else an eighth of the
+// array (512^3 FP32: 3.5 GB of 52.6), and never more than an eighth of the free device memory.
+constexpr size_t PAIR_WS_WHOLE = (size_t)2 << 30;
+
+// Whether `L` advances by paired passes; the first call decides and allocates (if it may).
+bool pair_ready(cnsf_lattice* L, bool may_alloc) {
+  if (L->own_launch) return false;
+  if (L->pair_decided || !may_alloc) return L->pair_ws != nullptr;
+  L->pair_decided = true;
+  size_t freeb = 0, total = 0;
+  int cus = 0;
+  if (hipMemGetInfo(&freeb, &total) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t budget = std::min(std::max(PAIR_WS_WHOLE, L->bytes / 8), freeb / 8);
+  if (!pair_plan(L->g, L->p.storage, budget, cus, &L->pair)) return false;
+  if (hipMalloc(&L->pair_ws, pair_workspace_bytes(L->g, L->p.storage, L->pair.split)) != hipSuccess) {
+    (void)hipGetLastError();   // single updates then
+    L->pair_ws = nullptr;
+  }
+  return L->pair_ws != nullptr;
 }
 
 // GRAPH_STEPS updates from even parity, captured on the lattice's own capture
@@ -368,6 +401,7 @@ int cnsf_destroy(cnsf_lattice* L) {
   if (L->spec) (void)hipFree(L->spec);
   if (L->step_partials) (void)hipFree(L->step_partials);
   if (L->dresult2) (void)hipFree(L->dresult2);
+  if (L->pair_ws) (void)hipFree(L->pair_ws);
   drop_graph(L);
   if (L->gstream) (void)hipStreamDestroy(L->gstream);
   delete L;
@@ -383,6 +417,7 @@ int cnsf_set_launch(cnsf_lattice* L, int32_t block, int32_t tile, int32_t grid, 
   L->lc.tile = tile;
   L->lc.grid = grid;
   L->lc.remap = xcd_remap ? 1 : 0;
+  L->own_launch = true;
   drop_graph(L);   // the captured updates carry the old shape
   return CNSF_OK;
 }
@@ -429,16 +464,25 @@ static int set_state_impl(cnsf_lattice* L, const double* Q, int32_t z0, int32_t 
   return CNSF_OK;
 }
 
-int cnsf_step(cnsf_lattice* L, int64_t n) {
-  if (!L) return fail(CNSF_E_INVALID, "lattice is NULL");
-  if (n < 0) return fail(CNSF_E_INVALID, "n = %lld < 0", (long long)n);
+// n >= 0 updates; may_pair: by paired passes where they are faster, may_alloc: their workspace
+// may be allocated now.
+static int step_impl(cnsf_lattice* L, int64_t n, bool may_pair, bool may_alloc) {
   (void)hipSetDevice(L->device);
   int64_t left = n;
   hipError_t e = hipSuccess;
   // a caller that is capturing its own stream gets plain launches in its graph
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (L->stream) (void)hipStreamIsCapturing(L->stream, &cap);
-  if (L->g.ncells <= GRAPH_MAX_CELLS && n >= 2 * GRAPH_STEPS && cap == hipStreamCaptureStatusNone) {
+  const bool plain = cap != hipStreamCaptureStatusNone;
+  if (!plain && may_pair && n - L->parity >= PAIR_STEPS && pair_ready(L, may_alloc)) {
+    if (L->parity) {
+      e = launch_steps(L, 1, L->stream, L->parity);
+      --left;
+    }
+    for (; e == hipSuccess && left >= PAIR_STEPS; left -= PAIR_STEPS)
+      for (int back = 0; back < 2 && e == hipSuccess; ++back)
+        e = launch_pair(L->p.storage, L->pop, L->pair_ws, L->g, L->ph, L->cd, L->pair, back != 0, L->stream);
+  } else if (!plain && L->g.ncells <= GRAPH_MAX_CELLS && n >= 2 * GRAPH_STEPS) {
     if (L->parity) {
       e = launch_steps(L, 1, L->stream, L->parity);
       --left;
@@ -453,17 +497,23 @@ int cnsf_step(cnsf_lattice* L, int64_t n) {
   return CNSF_OK;
 }
 
+int cnsf_step(cnsf_lattice* L, int64_t n) {
+  if (!L) return fail(CNSF_E_INVALID, "lattice is NULL");
+  if (n < 0) return fail(CNSF_E_INVALID, "n = %lld < 0", (long long)n);
+  return step_impl(L, n, true, true);
+}
+
 int cnsf_probe_update_ms(cnsf_lattice* L, int32_t steps, double* ms) {
   if (!L || !ms) return fail(CNSF_E_INVALID, "NULL argument");
   if (steps < 1) return fail(CNSF_E_INVALID, "steps = %d < 1", steps);
   (void)hipSetDevice(L->device);
-  if (int r = cnsf_step(L, 1)) return r;
+  if (int r = step_impl(L, 1, false, false)) return r;
   hipEvent_t a = nullptr, b = nullptr;
   hipError_t e = hipEventCreate(&a);
   if (e == hipSuccess) e = hipEventCreate(&b);
   if (e == hipSuccess) e = hipEventRecord(a, L->stream);
   int r = CNSF_OK;
-  if (e == hipSuccess) r = cnsf_step(L, steps);
+  if (e == hipSuccess) r = step_impl(L, steps, false, false);   // the single update is what is timed
   if (e == hipSuccess && r == CNSF_OK) e = hipEventRecord(b, L->stream);
   if (e == hipSuccess && r == CNSF_OK) e = hipEventSynchronize(b);
   float t = 0.0f;
@@ -689,7 +739,7 @@ int cnsf_step_diagnostics_static(cnsf_lattice* L, int64_t n, cnsf_diag* d) {
   ++L->step;
   e = launch_diag_final(sp, (int)nb, sp + STATIC_PARTIALS, L->stream);
   if (e != hipSuccess) return hip_fail(e, "diagnostic reduction");
-  if (int r = cnsf_step(L, n - 1)) return r;
+  if (int r = step_impl(L, n - 1, true, false)) return r;
   DiagPartial r{};
   e = hipMemcpyAsync(&r, sp + STATIC_PARTIALS, sizeof r, hipMemcpyDeviceToHost, L->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(L->stream);

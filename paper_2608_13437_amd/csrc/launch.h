@@ -29,6 +29,18 @@ hipError_t launch_moments(int storage, const void* pop, double* out, const Geom&
                           uint32_t cell0, uint32_t nslab, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 
+// Two updates in one pass (pair.hip): planes of the workspace, planes per launch, planes per block.
+struct PairPlan {
+  int split = 0, slab = 0, chunk = 0;
+};
+// The plan of a lattice with at most `budget` workspace bytes on `cus` compute units; false if
+// single updates are at least as fast or the lattice is not served.
+bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out);
+size_t pair_workspace_bytes(const Geom& g, int storage, int split);
+// One pass of a lattice at an even level: forward from the array to the shifted place, or back.
+hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd,
+                       const PairPlan& pl, bool back, hipStream_t s);
+
 // Diagnostics: FP64 sums and the spectral dissipation averages.
 struct DiagPartial {
   double mass, mx, my, mz, energy, ek2;  // ek2 = sum rho |u|^2

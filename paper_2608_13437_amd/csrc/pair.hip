@@ -1,0 +1,468 @@
+// Two updates in one pass over memory, for periodic lattices at an even time level.
+//
+// The single update moves every population through HBM twice per step (784 bytes per FP32 cell)
+// and is bound by that.  Here a block advances a column of the lattice by two steps while its
+// populations are on the chip: it walks PTX x PTY columns plane by plane along z, collides plane
+// z of level t (the columns around the tile too: D3Q7 needs the four faces, no corners), hands
+// the links on through LDS (x and y) and per-thread storage (z), collides plane z - 1 of level
+// t + 1 from them and streams the result into the neighbours' slots, i.e. level t + 2 in the
+// layout of an even level.  Stored values pass through the storage format between the two
+// steps, so the result is that of two single updates bit for bit.
+//
+// A pass reads and writes other memory (neighbouring tiles read what a tile would overwrite):
+//  * the whole lattice into a second array of its size and back in the next pass, or
+//  * for large lattices, slab by slab into the place `split` planes further down, the first
+//    planes into a workspace of `split` planes: slab s overwrites planes that slab s - 1 was the
+//    last to read.  The next pass goes the other way, from the top, and brings every plane home.
+// Passes therefore come in pairs, four updates, and between calls the array is as it always is.
+// The periodic end in z is the one place where order matters: the plane that the last slab
+// reads across the end is copied aside first, and the links that the first slab sends across it
+// are parked until their plane is free.
+//
+// Tile.  64 x 4 columns are 256 threads, plus 136 ring columns in three more waves; 7 waves of
+// up to 256 registers and 75 (FP32: 154) KiB of LDS are one block per CU.  Every x-row of a tile
+// also touches the 128-byte lines of its two ring cells, which are whole lines of the
+// neighbouring tiles: they are cheap only while both blocks are at the same plane and the line is
+// in their XCD's L2 (tiles of one XCD are a contiguous patch).  Non-temporal stores keep the
+// written planes from pushing those lines out.  512^3 FP32, array fetched over its size per pass
+// and time per update: 32 x 8 tiles 1.99x, 64 x 4 tiles 1.46x (1.84x with ordinary stores).
+// The next plane's loads are issued before the second collision (13.9 ms per update instead of
+// 14.5 without, same array).
+// Measured on MI355X per update, single updates -> pairs: 512^3 FP32 17.6 -> 11.1 ms on a fast
+// array, 20.8 -> 13.7 ms on a plain one; FP16 10.5 -> 8.4 ms (plain); 256^3 FP32 2.61 -> 1.52 ms,
+// FP16 1.27 -> 1.04 ms; 128^3 FP32 0.336 -> 0.197 ms.  What bounds it now: FP32 the fetch above,
+// 16-bit the vector units (7 + 4 wave collisions per 256 cells, 4.4 of 7.3 us a plane).
+#include <algorithm>
+#include <type_traits>
+
+#include "cnsf_impl.h"
+#include "launch.h"
+
+namespace cnsf {
+
+constexpr int PTX = 64, PTY = 4;              // interior columns of a tile along x and y
+constexpr int PNI = PTX * PTY;                // interior threads
+constexpr int PNR = 2 * PTX + 2 * PTY;        // ring threads
+constexpr int PNT = PNI + (PNR + 63) / 64 * 64;
+
+// Where a level of the lattice is stored: planes z < split in `scr` (cell index as in the
+// lattice), the others in `arr`, split planes further down than in the lattice.
+template <typename T>
+struct Place {
+  T *arr, *scr;
+  uint64_t cs_arr, cs_scr;   // elements between component regions
+  int split;
+};
+
+template <typename T>
+__device__ inline void plane_of(const Place<T>& p, int z, uint32_t nxy, T*& base, uint64_t& cs, uint32_t& cell0) {
+  if (z < p.split) {
+    base = p.scr;
+    cs = p.cs_scr;
+    cell0 = (uint32_t)z * nxy;
+  } else {
+    base = p.arr;
+    cs = p.cs_arr;
+    cell0 = (uint32_t)(z - p.split) * nxy;
+  }
+}
+
+template <typename T>
+__device__ inline __amdgpu_buffer_rsrc_t region_rsrc(T* base, uint64_t cs, int k) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(base + (uint64_t)k * cs), (short)0, (int)(uint32_t)(cs * sizeof(T)),
+                                           BUF_WORD3);
+}
+
+// The stored code as it is (16-bit codes are decoded only when they are needed: a conversion
+// right after the load would wait for it).
+template <int ST>
+__device__ inline typename Store<ST>::T load_code(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (ST == 0) {
+    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  } else {
+    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
+  }
+}
+
+constexpr int AUX_NT = 2;   // non-temporal
+template <int ST>
+__device__ inline void store_nt(__amdgpu_buffer_rsrc_t r, uint32_t off, float v) {
+  if constexpr (ST == 0) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, (int)off, 0, AUX_NT);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b16((short)Store<ST>::enc(v), r, (int)off, 0, AUX_NT);
+  }
+}
+
+// What a store to the array and a load from it do to a shifted population.
+template <int ST, bool SC>
+__device__ inline typename Store<ST>::T encode(const Codec& cd, int k, float v) {
+  if (ST != 0 && SC) v *= cd.inv_scale[k];
+  return Store<ST>::enc(v);
+}
+template <int ST, bool SC>
+__device__ inline float decode(const Codec& cd, int k, typename Store<ST>::T c) {
+  float v = Store<ST>::dec(c);
+  if (ST != 0 && SC) v *= cd.scale[k];
+  return v;
+}
+
+// One block: planes [za, zb) of one tile, za - 1 and zb being read too.  Planes of one launch:
+// [z_lo, z_hi), `chunk` per block.  Plane wrap_z (one past an end) is read from `wrap`, the
+// links to plane over_z are written to `over`.
+template <int ST, bool SC>
+__global__ void __launch_bounds__(PNT, 2)
+k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T> dst, const Geom g, const Phys ph,
+       const Codec cd, int z_lo, int z_hi, int chunk, int ntx, int ncol, const typename Store<ST>::T* __restrict__ wrap,
+       int wrap_z, typename Store<ST>::T* __restrict__ over, int over_z) {
+  using T = typename Store<ST>::T;
+  constexpr int NI = PNI, TY = PTY, PF = ST == 0 ? 6 : 7;   // components fetched ahead: as many as fit 256 VGPRs
+  __shared__ T xl[2][NC * 4 * NI];   // links along x and y of the last two planes collided, by destination cell
+  // links kept by their own thread: rest links (the last RB planes, by z mod RB) and +z links
+  // (the last UB planes, by z mod UB).  16-bit links leave room to store a plane's own while the
+  // older ones are still needed; FP32 links wait in registers until those are consumed.
+  constexpr bool EARLY = ST != 0;
+  constexpr int RB = EARLY ? 2 : 1, UB = EARLY ? 3 : 2;
+  __shared__ T zl[NC * (RB + UB) * NI];
+  // tile: XCD j takes a contiguous span of tiles of one chunk after the other
+  const uint32_t nb = gridDim.x, per = nb / 8u, rem = nb % 8u, xj = blockIdx.x & 7u, xq = blockIdx.x >> 3;
+  const uint32_t t = xj * per + (xj < rem ? xj : rem) + xq;
+  const int ch = (int)(t / (uint32_t)ncol), col = (int)(t % (uint32_t)ncol);
+  const int x0 = (col % ntx) * PTX, y0 = (col / ntx) * TY;
+  const int w = min(PTX, (int)g.nx - x0), h = min(TY, (int)g.ny - y0);
+  const int za = z_lo + ch * chunk, zb = min(z_hi, za + chunk);
+
+  const int tid = (int)threadIdx.x;
+  const bool inner = __builtin_amdgcn_readfirstlane(tid) < NI;
+  int lx, ly, rdir = 0, rdst = 0;   // tile coordinates; ring threads: link they hand in and its destination
+  bool live;
+  if (inner) {
+    lx = tid % PTX;
+    ly = tid / PTX;
+    live = lx < w && ly < h;
+  } else {
+    const int r = tid - NI;
+    if (r < PTX) { lx = r; ly = -1; rdir = 2; rdst = r; live = r < w; }
+    else if (r < 2 * PTX) { lx = r - PTX; ly = h; rdir = 3; rdst = (h - 1) * PTX + lx; live = lx < w; }
+    else if (r < 2 * PTX + TY) { lx = -1; ly = r - 2 * PTX; rdir = 0; rdst = ly * PTX; live = ly < h; }
+    else { lx = w; ly = r - 2 * PTX - TY; rdir = 1; rdst = ly * PTX + w - 1; live = ly < h; }
+    if (r >= PNR) live = false;
+  }
+  int gx = x0 + lx, gy = y0 + ly;
+  gx = gx < 0 ? gx + (int)g.nx : (gx >= (int)g.nx ? gx - (int)g.nx : gx);
+  gy = gy < 0 ? gy + (int)g.ny : (gy >= (int)g.ny ? gy - (int)g.ny : gy);
+  const uint32_t cxy = live ? (uint32_t)gy * g.nx + (uint32_t)gx : 0u;
+  // in-plane neighbours of the interior column
+  const uint32_t rowx = cxy - (uint32_t)gx;
+  const uint32_t cxp = gx == (int)g.nx - 1 ? rowx : cxy + 1u, cxm = gx == 0 ? cxy + (g.nx - 1u) : cxy - 1u;
+  const uint32_t cyp = gy == (int)g.ny - 1 ? (uint32_t)gx : cxy + g.nx;
+  const uint32_t cym = gy == 0 ? cxy + (g.nxy - g.nx) : cxy - g.nx;
+  constexpr uint32_t DEAD = 0xFFFF0000u;   // beyond every region: loads give 0, stores are dropped
+
+  T c[NC][NV];   // stored codes of the next plane, in flight
+  const T* lbase;
+  uint64_t lcs;
+  uint32_t lo;
+  auto aim = [&](int z) {   // where plane z of level t is
+    if (z == wrap_z) {
+      lbase = wrap;
+      lcs = (uint64_t)NV * ((g.nxy + SLOT_GROUP - 1) / SLOT_GROUP * SLOT_GROUP);
+      lo = slot_offset<ST>(g, 0, cxy);
+    } else {
+      T* b;
+      uint32_t c0;
+      plane_of(src, z < 0 ? z + (int)g.nz : (z >= (int)g.nz ? z - (int)g.nz : z), g.nxy, b, lcs, c0);
+      lbase = b;
+      lo = slot_offset<ST>(g, 0, c0 + cxy);
+    }
+    lo = live ? lo : DEAD;
+  };
+  auto fetch = [&](auto K0, auto K1) {
+#pragma unroll
+    for (int k = decltype(K0)::value; k < decltype(K1)::value; ++k) {
+      const __amdgpu_buffer_rsrc_t rs = region_rsrc(lbase, lcs, k);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        c[k][i] = load_code<ST>(rs, lo + (uint32_t)(i * SLOT_GROUP * sizeof(T)));
+      }
+    }
+  };
+  aim(za - 1);
+  fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, PF>{});
+
+  for (int z = za - 1; z <= zb; ++z) {
+    const bool links = z >= za && z < zb;   // the plane's x and y links are needed
+    fetch(std::integral_constant<int, PF>{}, std::integral_constant<int, NC>{});
+    float f[NC][NV];
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+#pragma unroll
+      for (int i = 0; i < NV; ++i) f[k][i] = decode<ST, SC>(cd, k, c[k][i]);
+    update_cell(f, cd, ph);
+    T* const Z = zl + tid;
+    const int rw = (z & 1) % RB, uw = RB + (z + UB) % UB;   // where plane z's own links go
+    const int rr = ((z - 1) & 1) % RB, ur = RB + (z + 2 * UB - 2) % UB;   // plane z - 1's rest, z - 2's +z links
+    T fm[NC], r0[NC], up[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      r0[k] = encode<ST, SC>(cd, k, f[k][0]);
+      up[k] = encode<ST, SC>(cd, k, f[k][5]);
+      fm[k] = encode<ST, SC>(cd, k, f[k][6]);
+    }
+    if (EARLY && inner) {
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        Z[(k * (RB + UB) + rw) * NI] = r0[k];
+        Z[(k * (RB + UB) + uw) * NI] = up[k];
+      }
+    }
+    T* xw = xl[z & 1];
+    if (links) {
+      if (inner) {
+        T* X = xw + tid;
+        if (live && lx + 1 < w)
+#pragma unroll
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 0) * NI + 1] = encode<ST, SC>(cd, k, f[k][1]);
+        if (live && lx > 0)
+#pragma unroll
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 1) * NI - 1] = encode<ST, SC>(cd, k, f[k][2]);
+        if (live && ly + 1 < h)
+#pragma unroll
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 2) * NI + PTX] = encode<ST, SC>(cd, k, f[k][3]);
+        if (live && ly > 0)
+#pragma unroll
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 3) * NI - PTX] = encode<ST, SC>(cd, k, f[k][4]);
+      } else if (live) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          const float v = rdir == 0 ? f[k][1] : (rdir == 1 ? f[k][2] : (rdir == 2 ? f[k][3] : f[k][4]));
+          xw[(k * 4 + rdir) * NI + rdst] = encode<ST, SC>(cd, k, v);
+        }
+      }
+    }
+    asm volatile("" ::: "memory");
+    if (z < zb) {
+      aim(z + 1);
+      fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, PF>{});
+    }
+    asm volatile("" ::: "memory");
+    // second update of plane z - 1: its links along z are in registers, along x and y in LDS
+    if (z > za && inner) {
+      const T* X = xl[(z - 1) & 1] + tid;
+      auto load = [&](int k, float e[NV]) {
+        e[0] = decode<ST, SC>(cd, k, Z[(k * (RB + UB) + rr) * NI]);
+#pragma unroll
+        for (int i = 1; i < 5; ++i) e[i] = decode<ST, SC>(cd, k, X[(k * 4 + i - 1) * NI]);
+        e[5] = decode<ST, SC>(cd, k, Z[(k * (RB + UB) + ur) * NI]);
+        e[6] = decode<ST, SC>(cd, k, fm[k]);
+      };
+      float dQ[NC], Q[NC], omega;
+      DevPrim P;
+      {
+        float e[NC][NV];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) load(k, e[k]);
+        omega = cell_state(e, cd, ph, dQ, Q, P);
+      }
+      asm volatile("" ::: "memory");   // the links are read again below instead of being held
+      // streamed into the neighbours' slots (level t + 2)
+      T* base[3];
+      uint64_t cs[3];
+      uint32_t o[NV], d0;
+      const int zp = z - 1;
+      plane_of(dst, zp, g.nxy, base[0], cs[0], d0);
+      o[0] = slot_offset<ST>(g, 0, d0 + cxy);
+      o[1] = slot_offset<ST>(g, 1, d0 + cxp);
+      o[2] = slot_offset<ST>(g, 2, d0 + cxm);
+      o[3] = slot_offset<ST>(g, 3, d0 + cyp);
+      o[4] = slot_offset<ST>(g, 4, d0 + cym);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int zn = zp + (j == 0 ? 1 : -1);
+        if (zn == over_z) {
+          // the plane across the periodic end, parked until its place is free
+          base[1 + j] = over;
+          cs[1 + j] = (g.nxy + SLOT_GROUP - 1) / SLOT_GROUP * SLOT_GROUP;
+          o[5 + j] = cxy * (uint32_t)sizeof(T);
+        } else {
+          plane_of(dst, zn < 0 ? zn + (int)g.nz : (zn >= (int)g.nz ? zn - (int)g.nz : zn), g.nxy, base[1 + j], cs[1 + j], d0);
+          o[5 + j] = slot_offset<ST>(g, 5 + j, d0 + cxy);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NV; ++i) o[i] = live ? o[i] : DEAD;
+      auto finish = [&](auto K) {
+        constexpr int k = decltype(K)::value;
+        float e[NV];
+        load(k, e);
+        collide_dev<k>(e, dQ, Q, P, ph, omega);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          const int j = i < 5 ? 0 : i - 4;
+          if (ST != 0 && SC) e[i] *= cd.inv_scale[k];
+          store_nt<ST>(region_rsrc(base[j], cs[j], k), o[i], e[i]);
+        }
+      };
+      finish(std::integral_constant<int, 0>{});
+      finish(std::integral_constant<int, 1>{});
+      finish(std::integral_constant<int, 2>{});
+      finish(std::integral_constant<int, 3>{});
+      finish(std::integral_constant<int, 4>{});
+      finish(std::integral_constant<int, 5>{});
+      finish(std::integral_constant<int, 6>{});
+      finish(std::integral_constant<int, 7>{});
+      finish(std::integral_constant<int, 8>{});
+      finish(std::integral_constant<int, 9>{});
+      finish(std::integral_constant<int, 10>{});
+      finish(std::integral_constant<int, 11>{});
+      finish(std::integral_constant<int, 12>{});
+      finish(std::integral_constant<int, 13>{});
+    }
+    if (!EARLY && inner) {
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        Z[(k * (RB + UB) + rw) * NI] = r0[k];
+        Z[(k * (RB + UB) + uw) * NI] = up[k];
+      }
+    }
+    __syncthreads();   // the links of plane z are in, those of plane z - 1 consumed
+  }
+}
+
+// One plane's stored populations, copied aside (98 slots; groups as in the lattice, cell 0 first).
+template <typename T>
+__global__ void __launch_bounds__(256) k_plane_save(const T* __restrict__ base, uint64_t cs, uint32_t cell0, uint32_t nxy,
+                                                    T* __restrict__ out, uint64_t ocs) {
+  const uint32_t c = blockIdx.x * 256u + threadIdx.x;
+  if (c >= nxy) return;
+  const uint32_t k = blockIdx.y;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) out[k * ocs + slot_index(i, c)] = base[k * cs + slot_index(i, cell0 + c)];
+}
+
+// The parked links of one direction, put into their plane.
+template <typename T>
+__global__ void __launch_bounds__(256) k_plane_put(const T* __restrict__ in, uint64_t ics, uint32_t nxy, int slot,
+                                                   T* __restrict__ base, uint64_t cs, uint32_t cell0) {
+  const uint32_t c = blockIdx.x * 256u + threadIdx.x;
+  if (c >= nxy) return;
+  const uint32_t k = blockIdx.y;
+  base[k * cs + slot_index(slot, cell0 + c)] = in[k * ics + c];
+}
+
+static uint64_t groups(uint64_t n) { return (n + SLOT_GROUP - 1) / SLOT_GROUP * SLOT_GROUP; }
+
+size_t pair_workspace_bytes(const Geom& g, int storage, int split) {
+  const size_t e = storage == 0 ? 4 : 2;
+  size_t n = (size_t)NP * groups((uint64_t)split * g.nxy);
+  if (split < (int)g.nz) n += (size_t)(NP + NC) * groups(g.nxy);   // the wrapped plane and the parked links
+  return n * e;
+}
+
+// How to cut a lattice, and whether two updates in one pass are faster than two single ones.
+// A launch takes rounds x (planes per block + 3) plane times: rounds are its blocks over the CUs,
+// a block reads one plane more at either end and needs about one plane time to start.  Measured
+// plane times (us, TGV boxes of 24^3 to 512^3): FP32 11.0 with full tiles and rows of whole
+// 128-byte lines (10.1-11.1), shorter as fewer of the tile's columns exist, about 4 more when a
+// row starts inside a 64-byte sector (13 at 150^3 and 200^3), 7.2 when the lattice fits the
+// 256 MB last-level cache; 16-bit 7.7 (7.3-8.1) and 2.4 more with rows of partial lines.  Single
+// updates (ns per cell): FP32 0.155 (0.12 in cache), 16-bit 0.077 (0.072).  Pairs must win by 5%:
+// taken at 64^3 FP32 (25 against 31 us per update), 96^3 (94 / 132), 128^3 (193 / 336; 16-bit
+// 139 / 163), 192^3 16-bit (469 / 553); left at 80^3 FP32 (70 / 62), 160^3 and 224^3 16-bit
+// (both equal).
+bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out) {
+  if (g.bc_x != 0) return false;
+  const size_t e = storage == 0 ? 4 : 2;
+  if (g.cstride * e > 0xFFFF0000ull) return false;   // dead lanes use offsets from there on
+  const int nz = (int)g.nz;
+  const int ncol = (int)((g.nx + PTX - 1) / PTX * ((g.ny + PTY - 1) / PTY));
+  int m = 1;   // planes that hold whole slot groups
+  while (m < (int)SLOT_GROUP && (uint64_t)m * g.nxy % SLOT_GROUP) m *= 2;
+  double best = 1e300;
+  auto consider = [&](int split, int slab) {
+    if (pair_workspace_bytes(g, storage, split) > budget) return;
+    const int nslab = (nz + slab - 1) / slab;
+    for (int c = 1; c <= std::min(slab, 64); ++c) {
+      const int h = (slab + c - 1) / c;
+      const int rounds = (ncol * ((slab + h - 1) / h) + cus - 1) / cus;
+      const double t = (double)nslab * rounds * (h + 3);
+      if (t < best) {
+        best = t;
+        out->split = split;
+        out->slab = slab;
+        out->chunk = h;
+      }
+    }
+  };
+  consider(nz, nz);
+  for (int n = 2; n * 4 <= nz && nz / n >= 4; ++n) {
+    const int slab = (nz + n - 1) / n, split = (slab + 2 + m - 1) / m * m;
+    if (split + 2 <= nz) consider(split, slab);
+  }
+  if (best > 1e299) return false;
+  const bool cached = (double)NP * e * g.ncells <= 256e6;
+  const size_t row = g.nx * e;
+  const double fill = (double)g.nxy / ((double)ncol * PNI);
+  double plane, cell;
+  if (storage == 0) {
+    plane = cached ? 7.2 : 11.0 * (0.2 + 0.8 * fill) + (row % 64 ? 4.0 : (row % 128 ? 2.0 : 0.0));
+    cell = cached ? 0.12 : 0.155;
+  } else {
+    plane = row % 128 ? 7.6 * (0.4 + 0.6 * fill) + 2.4 : 7.7;
+    cell = cached ? 0.072 : 0.077;
+  }
+  return 1.05 * best * plane < 2e-3 * cell * g.ncells;
+}
+
+template <int ST, bool SC>
+static hipError_t launch_pair_t(void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd, const PairPlan& pl,
+                                bool back, hipStream_t s) {
+  using T = typename Store<ST>::T;
+  const bool whole = pl.split >= (int)g.nz;
+  const uint64_t cs_scr = (uint64_t)NV * groups((uint64_t)pl.split * g.nxy);
+  T* scr = (T*)ws;
+  T* wrap = scr + NC * cs_scr;
+  T* over = wrap + (uint64_t)NP * groups(g.nxy);
+  const Place<T> home{(T*)pop, scr, g.cstride, cs_scr, 0}, moved{(T*)pop, scr, g.cstride, cs_scr, pl.split};
+  const Place<T> src = back ? moved : home, dst = back ? home : moved;
+  const int nz = (int)g.nz, none = -1000000;
+  const int wrap_z = whole ? none : (back ? -1 : nz), over_z = whole ? none : (back ? nz : -1);
+  auto cell = [&](const Place<T>& p, int z, T*& b, uint64_t& cs) {
+    b = z < p.split ? p.scr : p.arr;
+    cs = z < p.split ? p.cs_scr : p.cs_arr;
+    return (uint32_t)(z < p.split ? z : z - p.split) * g.nxy;
+  };
+  const dim3 pg((g.nxy + 255) / 256, NC);
+  if (!whole) {
+    T* b;
+    uint64_t cs;
+    const uint32_t c0 = cell(src, back ? nz - 1 : 0, b, cs);
+    hipLaunchKernelGGL(k_plane_save<T>, pg, dim3(256), 0, s, (const T*)b, cs, c0, g.nxy, wrap, (uint64_t)NV * groups(g.nxy));
+  }
+  const int ntx = ((int)g.nx + PTX - 1) / PTX, ncol = ntx * (((int)g.ny + PTY - 1) / PTY);
+  const int nslab = (nz + pl.slab - 1) / pl.slab;
+  for (int j = 0; j < nslab; ++j) {
+    const int q = back ? nslab - 1 - j : j;
+    const int z0 = q * pl.slab, z1 = std::min(nz, z0 + pl.slab);
+    const int nch = (z1 - z0 + pl.chunk - 1) / pl.chunk;
+    hipLaunchKernelGGL((k_pair<ST, SC>), dim3(ncol * nch), dim3(PNT), 0, s, src, dst, g, ph, cd, z0, z1,
+                       pl.chunk, ntx, ncol, (const T*)wrap, wrap_z, over, over_z);
+  }
+  if (!whole) {
+    T* b;
+    uint64_t cs;
+    const uint32_t c0 = cell(dst, back ? 0 : nz - 1, b, cs);
+    hipLaunchKernelGGL(k_plane_put<T>, pg, dim3(256), 0, s, (const T*)over, groups(g.nxy), g.nxy, back ? 5 : 6, b, cs, c0);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd,
+                       const PairPlan& pl, bool back, hipStream_t s) {
+  const bool sc = cd.scaled != 0;
+  if (storage == 0) return launch_pair_t<0, false>(pop, ws, g, ph, cd, pl, back, s);
+  if (storage == 1) return (sc ? launch_pair_t<1, true> : launch_pair_t<1, false>)(pop, ws, g, ph, cd, pl, back, s);
+  return (sc ? launch_pair_t<2, true> : launch_pair_t<2, false>)(pop, ws, g, ph, cd, pl, back, s);
+}
+
+}  // namespace cnsf

@@ -1,0 +1,103 @@
+"""Multi-step calls that advance two updates per pass over memory, against single updates.
+
+The paired passes must leave every stored population bit for bit as single
+updates do.  Cases sit where the cut of the lattice can go wrong: one tile and
+several along x and y with ragged last tiles, one and several blocks along z,
+a second array of the lattice's size and slabs shifted through a workspace
+(whose first and last planes cross the periodic end by their own route), an
+odd level at entry and every remainder of the step count.  Setting the launch
+shape of the update (to its default) keeps a lattice on single updates, which
+gives the reference; a drop of the free device memory shows that the other
+lattice did allocate the workspace of the paired passes.
+"""
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _cnsf():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2608_13437_amd as cnsf
+    cnsf.library()
+    return cnsf
+
+
+def _state(prm, seed):
+    """Random positive state on the device (every cell its own sensor decision)."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    sh = (prm["nz"], prm["ny"], prm["nx"])
+    r = lambda a: a * (2 * torch.rand(sh, generator=g, device="cuda", dtype=torch.float64) - 1)
+    rho, p = 1.0 + r(0.4), 1.0 + r(0.4)
+    u = [r(0.3) for _ in range(3)]
+    Q = torch.empty((14,) + sh, device="cuda", dtype=torch.float64)
+    Q[0] = rho
+    for a in range(3):
+        Q[1 + a] = rho * u[a]
+    Q[4] = p / (prm["gamma"] - 1.0) + 0.5 * rho * (u[0] ** 2 + u[1] ** 2 + u[2] ** 2)
+    for k in range(5, 14):
+        Q[k] = r(0.01)
+    return Q
+
+
+# nx, ny, nz, storage, storage scale, steps per call
+CASES = [
+    (64, 64, 64, W.STORAGE_FP32, 0.0, (1, 5, 4, 7)),      # one tile along x, second array
+    (96, 94, 100, W.STORAGE_FP32, 0.0, (4, 6)),           # half a tile, two rows in the last one
+    (128, 128, 127, W.STORAGE_FP16, 0.0, (4, 3, 9)),      # 16-bit links
+    (128, 128, 128, W.STORAGE_BF16, 0.0, (8,)),
+    (128, 126, 128, W.STORAGE_FP16, 0.5, (5, 4)),         # scaled codes, two rows in the last tile
+    (192, 192, 192, W.STORAGE_FP32, 0.0, (4, 1, 10)),     # slabs through a workspace
+    (256, 254, 192, W.STORAGE_FP32, 0.0, (4, 5)),         # slabs of whole slot groups, two rows in the last tile
+    (320, 256, 256, W.STORAGE_FP16, 0.0, (4, 6)),         # 16-bit slabs
+]
+
+
+@pytest.mark.parametrize("nx,ny,nz,storage,scale,calls", CASES)
+def test_paired_passes_equal_single_updates(nx, ny, nz, storage, scale, calls):
+    import torch
+    cnsf = _cnsf()
+    prm = dict(W.random_params(nx, ny, nz, seed=3), storage=storage, storage_scale=[scale] * 14)
+    print(f"case {nx}x{ny}x{nz} storage {storage} scale {scale} calls {calls}", flush=True)
+    Q = _state(prm, 17)
+    a, b = cnsf.Lattice(prm), cnsf.Lattice(prm)
+    a.set_state(Q)
+    b.set_state(Q)
+    del Q
+    a.set_launch(*a.get_launch())
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    for n in calls:
+        b.step(n)
+    torch.cuda.synchronize()
+    taken = free0 - torch.cuda.mem_get_info()[0]
+    for n in calls:
+        a.step(n)
+    assert taken >= a.nbytes // 32, f"single updates ran: {taken} bytes taken"
+    assert a.info()[:2] == b.info()[:2]
+    assert torch.equal(a.buf, b.buf)
+    assert bool(torch.isfinite(b.moments(device=True)).all())
+    a.close()
+    b.close()
+
+
+def test_paired_passes_give_their_workspace_back():
+    import torch
+    cnsf = _cnsf()
+    prm = W.random_params(128, 128, 128)
+    Q = _state(prm, 5)
+    torch.cuda.synchronize()
+    free = []
+    for _ in range(3):
+        L = cnsf.Lattice(prm)
+        L.set_state(Q)
+        L.step(8)
+        L.close()
+        del L
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+    assert abs(free[2] - free[1]) < 64 << 20
