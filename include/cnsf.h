@@ -223,7 +223,7 @@ int cnsf_diagnostics(cnsf_lattice* lat, int32_t flags, cnsf_diag* out);
  * cnsf_spectrum_shells gives the shell count 1 + nint(sqrt(3) * (n / 2)).
  * E (host or device) holds nshells >= that count values; entries beyond it
  * are zero.  Uses the spectral workspace of cnsf_diagnostics (allocated on
- * first use) and nz * shells doubles more.  CNSF_E_INVALID unless nx = ny =
+ * first use) and 4 * nz * shells doubles more.  CNSF_E_INVALID unless nx = ny =
  * nz with bc_x = PERIODIC; CNSF_E_SIZE if nshells is too small. */
 int cnsf_spectrum_shells(const cnsf_lattice* lat, int32_t* nshells);
 int cnsf_spectrum(cnsf_lattice* lat, double* E, int32_t nshells, int32_t where);

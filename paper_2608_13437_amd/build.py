@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(ROOT, "_build", "cnsf")
 LIB = os.path.join(PKG, "libcnsf.so")
 
-SOURCES = ["api.cpp", "layout.cpp", "update.hip", "pair.hip", "diag.hip", "batch.hip"]
+SOURCES = ["api.cpp", "layout.cpp", "update.hip", "pair.hip", "diag.hip", "lines.hip", "batch.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -25,6 +25,9 @@ HIPCC_FLAGS = [
     # fuse multiply-add only inside one source expression, so that every
     # kernel that inlines the same cell update rounds it the same way
     "-ffp-contract=on",
+    # matrix-unit accumulators stay in vector registers (lines.hip: with them in accumulation
+    # registers every loop iteration copied them there and back)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
     "-I", os.path.join(ROOT, "include"),
 ]

@@ -771,7 +771,7 @@ int cnsf_spectrum(cnsf_lattice* L, double* E, int32_t nshells, int32_t where) {
       return fail(CNSF_E_NOMEM, "spectral workspace: %s", hipGetErrorString(e));
     }
   }
-  const size_t npart = (size_t)L->g.nz * (size_t)need;
+  const size_t npart = (size_t)SHELL_PARTS * L->g.nz * (size_t)need;
   if (!L->spec) {
     e = hipMalloc(&L->spec, (npart + (size_t)need) * sizeof(double));
     if (e != hipSuccess) {

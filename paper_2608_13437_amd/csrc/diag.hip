@@ -4,8 +4,9 @@
 // mu_T, accumulate mass, momentum, energy, rho |u|^2, minima, non-finite and
 // sensor-active counts into one partial per block (fixed grid, grid-stride),
 // and optionally write u, v, w, mu_T to the spectral workspace.
-// Passes 2-4 (spectral): for each axis, every line of the periodic box is
-// transformed in LDS (radix-2 FFT for power-of-two lengths, otherwise a
+// Passes 2-4 (spectral): for each axis, every line of the periodic box goes
+// through a matrix product (lines.hip: most lengths), or is
+// transformed in LDS (radix-2 FFT for larger power-of-two lengths, otherwise a
 // direct sum with the trigonometric-interpolant derivative kernel), multiplied
 // by i k (the Nyquist mode of an even length differentiates to zero) and
 // transformed back; derivatives accumulate into div u and curl u.  The last
@@ -17,6 +18,7 @@
 #include "cnsf_impl.h"
 #include "diag_common.h"
 #include "launch.h"
+#include "lines.h"
 
 namespace cnsf {
 
@@ -833,14 +835,16 @@ __global__ void __launch_bounds__(64 * W512) k_spectrum512(const double* __restr
 // Integer wavenumber of DFT index j on an axis of n points.
 __device__ inline int64_t wavenumber(uint32_t j, uint32_t n) { return j < (n + 1) / 2 ? (int64_t)j : (int64_t)j - n; }
 
-// Shell sums of one kappa_z plane per block, in a fixed order.  Along a row of
+// Shell sums of a part of one kappa_z plane per block, in a fixed order.  Along a row of
 // fixed (kappa_y, kappa_z) the shell nint(|kappa|) never decreases with
 // |kappa_x|, so a wave takes 64 consecutive |kappa_x| (both signs together),
 // sums each run of equal shells with a segmented scan, and adds the run totals
-// to its own LDS histogram (shells within one chunk are distinct).  Wave w
-// takes rows w, w + 4, ...; the block adds its four histograms in order.
-__global__ void __launch_bounds__(DB) k_shell_partials(const double* __restrict__ energy, uint32_t n, uint32_t nshells,
-                                                       double* __restrict__ partial) {
+// to its own LDS histogram (shells within one chunk are distinct).  Block (z, b) of gridDim.y
+// parts takes rows 4 b + w, 4 (b + gridDim.y) + w, ... in wave w and adds its four histograms in
+// order.  Rows of n/2 + 1 energies (row_len < n) hold kappa_x >= 0 only; the opposite sign holds
+// the same.  Four parts to a plane: with one, 192 blocks of 4 waves took 72 us at 192^3.
+__global__ void __launch_bounds__(DB) k_shell_partials(const double* __restrict__ energy, uint32_t n, uint32_t row_len,
+                                                       uint32_t nshells, double* __restrict__ partial) {
   extern __shared__ double hist[];   // 4 x nshells
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   for (uint32_t s = threadIdx.x; s < 4 * nshells; s += blockDim.x) hist[s] = 0.0;
@@ -849,10 +853,10 @@ __global__ void __launch_bounds__(DB) k_shell_partials(const double* __restrict_
   const int64_t mz = wavenumber(jz, n);
   const uint32_t tmax = n / 2;      // largest |kappa_x|
   double* h = hist + wave * nshells;
-  for (uint32_t jy = wave; jy < n; jy += 4) {
+  for (uint32_t jy = 4 * blockIdx.y + wave; jy < n; jy += 4 * gridDim.y) {
     const int64_t my = wavenumber(jy, n);
     const int64_t c2 = my * my + mz * mz;
-    const double* row = energy + ((uint64_t)jz * n + jy) * n;
+    const double* row = energy + ((uint64_t)jz * n + jy) * row_len;
     for (uint32_t t0 = 0; t0 <= tmax; t0 += 64) {
       const uint32_t t = t0 + lane;
       const bool valid = t <= tmax;
@@ -861,7 +865,7 @@ __global__ void __launch_bounds__(DB) k_shell_partials(const double* __restrict_
       if (valid) {
         key = (int)floor(sqrt((double)((int64_t)t * t + c2)) + 0.5);
         val = row[t];
-        if (t != 0 && n - t != t) val += row[n - t];
+        if (t != 0 && n - t != t) val += row_len < n ? val : row[n - t];
       }
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
@@ -874,20 +878,22 @@ __global__ void __launch_bounds__(DB) k_shell_partials(const double* __restrict_
     }
   }
   __syncthreads();
+  double* out = partial + ((uint64_t)jz * gridDim.y + blockIdx.y) * nshells;
   for (uint32_t s = threadIdx.x; s < nshells; s += blockDim.x)
-    partial[(uint64_t)jz * nshells + s] = ((hist[s] + hist[nshells + s]) + hist[2 * nshells + s]) + hist[3 * nshells + s];
+    out[s] = ((hist[s] + hist[nshells + s]) + hist[2 * nshells + s]) + hist[3 * nshells + s];
 }
 
-// E[k] = sum over planes of the partial shell sums, planes in order; zero for
-// k >= nshells up to nout.
-__global__ void k_shell_final(const double* __restrict__ partial, uint32_t nplanes, uint32_t nshells, uint32_t nout,
-                              double* __restrict__ E) {
-  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+// E[k] = sum over the parts' shell sums, one wave per shell, parts dealt to the lanes and the
+// lanes added in a fixed order; zero for k >= nshells up to nout.
+__global__ void __launch_bounds__(DB) k_shell_final(const double* __restrict__ partial, uint32_t nparts, uint32_t nshells,
+                                                    uint32_t nout, double* __restrict__ E) {
+  const uint32_t k = blockIdx.x * (DB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
   if (k >= nout) return;
   double acc = 0.0;
   if (k < nshells)
-    for (uint32_t p = 0; p < nplanes; ++p) acc += partial[(uint64_t)p * nshells + k];
-  E[k] = acc;
+    for (uint32_t p = lane; p < nparts; p += 64) acc += partial[(uint64_t)p * nshells + k];
+  acc = wave_sum(acc);
+  if (lane == 0) E[k] = acc;
 }
 
 // Sums of consecutive chunks of partials, one block per chunk, in a fixed order.
@@ -961,46 +967,79 @@ hipError_t launch_spectral(const Geom& g, double dx, double* fields, DiagPartial
   // complete each field (omega_z in the second y pass, omega_y, omega_x and
   // div u in the z passes), which add mu field^2 to the block partials instead
   // of storing the field; the first of them initialises the partials' eps fields.
-  const bool fuse_eps = g.ny == 512 && g.nz == 512 && CNSF_DERIV_512;
+  // Lines served by the matrix products (lines.hip) take the same route, three components of an
+  // axis to a launch, when both y and z are of that kind.
+  const bool lines_yz = deriv_lines_serves(g.ny) && deriv_lines_serves(g.nz);
+  const bool fuse_eps = lines_yz || (g.ny == 512 && g.nz == 512 && CNSF_DERIV_512);
   int first_sum = 1;
-  for (const Pass& ps : passes) {
-    DerivAxis da{};
-    da.n = dims[ps.a];
-    da.stride = strides[ps.a];
-    da.nlines = (uint32_t)(N / da.n);
-    uint32_t lg = 0;
-    while ((1u << lg) < da.n) ++lg;
-    da.log2n = ((1u << lg) == da.n && da.n >= 2) ? lg : 0;
-    // LDS: one (FFT) or two (direct) complex rows per line pair, plus the
-    // twiddle table (FFT) or the derivative kernel (direct), <= 64 KiB
-    const uint32_t rows = da.log2n ? 1u : 2u;
-    const uint32_t extra = da.log2n ? (da.n - 1) * 16u : (da.n + 2) * 8u;
-    uint32_t tp = ((uint32_t)CNSF_DERIV_LDS - extra) / (rows * lds_line(da.n) * 16u);
-    if (ps.a == 0 && CNSF_DERIV_PAIRS_X > 0 && (uint32_t)CNSF_DERIV_PAIRS_X < tp) tp = CNSF_DERIV_PAIRS_X;
-    if (ps.a != 0 && CNSF_DERIV_PAIRS_YZ > 0 && (uint32_t)CNSF_DERIV_PAIRS_YZ < tp) tp = CNSF_DERIV_PAIRS_YZ;
-    da.pairs_per_block = tp < 1 ? 1 : (tp > 16 ? 16 : tp);
-    da.axis = ps.a;
-    da.init = ps.init;
-    da.sign = ps.sign;
-    da.kscale = 2.0 * M_PI / ((double)da.n * dx);
-    const size_t lds = (size_t)rows * da.pairs_per_block * lds_line(da.n) * sizeof(double2) + extra;
-    const int k = (int)(&ps - passes);
-    if (fuse_eps && (k == 3 || k >= 6)) {
-      da.eps = first_sum ? (full ? 2 : 3) : 1;
-      da.eps_d = ps.target == 0;
-      first_sum = 0;
+  for (int a = 0; a < 3; ++a) {
+    if (deriv_lines_serves(dims[a])) {
+      LineDeriv ld{};
+      ld.n = dims[a];
+      ld.stride = strides[a];
+      ld.nlines = (uint32_t)(N / ld.n);
+      ld.nx = g.nx;
+      ld.nxy = g.nxy;
+      ld.axis = a;
+      ld.full = full;
+      ld.mu = 3 * N;
+      ld.kscale = 2.0 * M_PI / ((double)ld.n * dx);
+      for (int q = 0; q < 3; ++q) {
+        const Pass& ps = passes[3 * a + q];
+        const int k = 3 * a + q;
+        LineComp& c = ld.c[q];
+        c.in = ps.c * N;
+        c.out = (4 + ps.target) * N;
+        c.sign = ps.sign;
+        c.init = ps.init;
+        c.eps = -1;
+        c.eps_d = ps.target == 0;
+        if (fuse_eps && (k == 3 || k >= 6)) c.eps = k == 3 ? 0 : k - 5;
+      }
+      const hipError_t e = launch_deriv_lines(ld, fields, partials, s);
+      if (e != hipSuccess) return e;
+      continue;
     }
-    if (da.n == 512 && CNSF_DERIV_512 && da.eps)
-      hipLaunchKernelGGL(k_deriv512<true>, dim3(DIAG_BLOCKS), dim3(64 * W512), 0, s, fields + ps.c * N,
-                         fields + (4 + ps.target) * N, g, da, (const double*)fields, partials);
-    else if (da.n == 512 && CNSF_DERIV_512)
-      hipLaunchKernelGGL(k_deriv512<false>, dim3(DIAG_BLOCKS), dim3(64 * W512), 0, s, fields + ps.c * N,
-                         fields + (4 + ps.target) * N, g, da, (const double*)fields, partials);
-    else
-      hipLaunchKernelGGL(k_deriv_axis, dim3(DIAG_BLOCKS), dim3(DB), lds, s, fields + ps.c * N,
-                         fields + (4 + ps.target) * N, g, da);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    for (int q = 0; q < 3; ++q) {
+      const int k = 3 * a + q;
+      const Pass& ps = passes[k];
+      DerivAxis da{};
+      da.n = dims[ps.a];
+      da.stride = strides[ps.a];
+      da.nlines = (uint32_t)(N / da.n);
+      uint32_t lg = 0;
+      while ((1u << lg) < da.n) ++lg;
+      da.log2n = ((1u << lg) == da.n && da.n >= 2) ? lg : 0;
+      // LDS: one (FFT) or two (direct) complex rows per line pair, plus the
+      // twiddle table (FFT) or the derivative kernel (direct), <= 64 KiB
+      const uint32_t rows = da.log2n ? 1u : 2u;
+      const uint32_t extra = da.log2n ? (da.n - 1) * 16u : (da.n + 2) * 8u;
+      uint32_t tp = ((uint32_t)CNSF_DERIV_LDS - extra) / (rows * lds_line(da.n) * 16u);
+      if (ps.a == 0 && CNSF_DERIV_PAIRS_X > 0 && (uint32_t)CNSF_DERIV_PAIRS_X < tp) tp = CNSF_DERIV_PAIRS_X;
+      if (ps.a != 0 && CNSF_DERIV_PAIRS_YZ > 0 && (uint32_t)CNSF_DERIV_PAIRS_YZ < tp) tp = CNSF_DERIV_PAIRS_YZ;
+      da.pairs_per_block = tp < 1 ? 1 : (tp > 16 ? 16 : tp);
+      da.axis = ps.a;
+      da.init = ps.init;
+      da.sign = ps.sign;
+      da.kscale = 2.0 * M_PI / ((double)da.n * dx);
+      const size_t lds = (size_t)rows * da.pairs_per_block * lds_line(da.n) * sizeof(double2) + extra;
+      if (fuse_eps && (k == 3 || k >= 6)) {
+        da.eps = first_sum ? (full ? 2 : 3) : 1;
+        da.eps_d = ps.target == 0;
+        first_sum = 0;
+      }
+      if (da.n == 512 && CNSF_DERIV_512 && da.eps)
+        hipLaunchKernelGGL(k_deriv512<true>, dim3(DIAG_BLOCKS), dim3(64 * W512), 0, s, fields + ps.c * N,
+                           fields + (4 + ps.target) * N, g, da, (const double*)fields, partials);
+      else if (da.n == 512 && CNSF_DERIV_512)
+        hipLaunchKernelGGL(k_deriv512<false>, dim3(DIAG_BLOCKS), dim3(64 * W512), 0, s, fields + ps.c * N,
+                           fields + (4 + ps.target) * N, g, da, (const double*)fields, partials);
+      else
+        hipLaunchKernelGGL(k_deriv_axis, dim3(DIAG_BLOCKS), dim3(DB), lds, s, fields + ps.c * N,
+                           fields + (4 + ps.target) * N, g, da);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   if (fuse_eps) return hipSuccess;
   hipLaunchKernelGGL(k_eps_sums, dim3(DIAG_BLOCKS), dim3(DB), 0, s, fields, g, partials, full ? 1 : 0);
@@ -1027,6 +1066,13 @@ hipError_t launch_spectrum(const Geom& g, double* fields, double* partial, doubl
   uint32_t tl = (65536u - extra) / (rows * lds_line(n) * 16u);
   tl = tl < 1 ? 1 : (tl > 16 ? 16 : tl);
   const double n3 = (double)N;
+  uint32_t row_len = n;
+  if (dft_lines_serves(n)) {
+    const hipError_t e = launch_dft_lines(n, fields, s);
+    if (e != hipSuccess) return e;
+    energy = fields;
+    row_len = n / 2 + 1;
+  } else
   for (int c = 0; c < 3; ++c) {
     for (int a = 0; a < 3; ++a) {
       SpecAxis sa{};
@@ -1051,10 +1097,12 @@ hipError_t launch_spectrum(const Geom& g, double* fields, double* partial, doubl
       if (e != hipSuccess) return e;
     }
   }
-  hipLaunchKernelGGL(k_shell_partials, dim3(n), dim3(DB), 4 * nshells * sizeof(double), s, energy, n, nshells, partial);
+  hipLaunchKernelGGL(k_shell_partials, dim3(n, SHELL_PARTS), dim3(DB), 4 * nshells * sizeof(double), s, energy, n, row_len,
+                     nshells, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_shell_final, dim3((nout + 255) / 256), dim3(256), 0, s, partial, n, nshells, nout, E);
+  hipLaunchKernelGGL(k_shell_final, dim3((nout + DB / 64 - 1) / (DB / 64)), dim3(DB), 0, s, partial, n * SHELL_PARTS,
+                     nshells, nout, E);
   return hipGetLastError();
 }
 

@@ -74,8 +74,9 @@ hipError_t launch_diag_final2(DiagPartial* partials, int nparts, DiagPartial* tm
                               hipStream_t s);
 // Shell spectrum of the velocity held in fields (u, v, w: the first 3 * ncells
 // doubles, written by launch_diag_sums); uses fields[4 ncells, 7 ncells) as
-// workspace and partial (nz * spectrum_shells(nx) doubles).  Writes nout
+// workspace and partial (SHELL_PARTS * nz * spectrum_shells(nx) doubles).  Writes nout
 // values to E (zero beyond the shell count).  Cubic periodic lattices only.
+constexpr uint32_t SHELL_PARTS = 4;
 uint32_t spectrum_shells(uint32_t n);
 hipError_t launch_spectrum(const Geom& g, double* fields, double* partial, double* E, uint32_t nout, hipStream_t s);
 
