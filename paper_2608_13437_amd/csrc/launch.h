@@ -29,9 +29,10 @@ hipError_t launch_moments(int storage, const void* pop, double* out, const Geom&
                           uint32_t cell0, uint32_t nslab, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 
-// Two updates in one pass (pair.hip): planes of the workspace, planes per launch, planes per block.
+// Two updates in one pass (pair.hip): planes of the workspace, planes per launch, planes per block,
+// columns of a tile along x and y.
 struct PairPlan {
-  int split = 0, slab = 0, chunk = 0;
+  int split = 0, slab = 0, chunk = 0, tx = 0, ty = 0;
 };
 // The plan of a lattice with at most `budget` workspace bytes on `cus` compute units; false if
 // single updates are at least as fast or the lattice is not served.

@@ -2,7 +2,7 @@
 //
 // The single update moves every population through HBM twice per step (784 bytes per FP32 cell)
 // and is bound by that.  Here a block advances a column of the lattice by two steps while its
-// populations are on the chip: it walks PTX x PTY columns plane by plane along z, collides plane
+// populations are on the chip: it walks a tile of columns plane by plane along z, collides plane
 // z of level t (the columns around the tile too: D3Q7 needs the four faces, no corners), hands
 // the links on through LDS (x and y) and per-thread storage (z), collides plane z - 1 of level
 // t + 1 from them and streams the result into the neighbours' slots, i.e. level t + 2 in the
@@ -19,18 +19,18 @@
 // reads across the end is copied aside first, and the links that the first slab sends across it
 // are parked until their plane is free.
 //
-// Tile.  64 x 4 columns are 256 threads, plus 136 ring columns in three more waves; 7 waves of
-// up to 256 registers and 75 (FP32: 154) KiB of LDS are one block per CU.  Every x-row of a tile
-// also touches the 128-byte lines of its two ring cells, which are whole lines of the
-// neighbouring tiles: they are cheap only while both blocks are at the same plane and the line is
-// in their XCD's L2 (tiles of one XCD are a contiguous patch).  Non-temporal stores keep the
-// written planes from pushing those lines out.  512^3 FP32, array fetched over its size per pass
-// and time per update: 32 x 8 tiles 1.99x, 64 x 4 tiles 1.46x (1.84x with ordinary stores).
-// The next plane's loads are issued before the second collision (13.9 ms per update instead of
-// 14.5 without, same array).
-// Measured on MI355X per update, single updates -> pairs: 512^3 FP32 17.6 -> 11.1 ms on a fast
-// array, 20.8 -> 13.7 ms on a plain one; FP16 10.5 -> 8.4 ms (plain); 256^3 FP32 2.61 -> 1.52 ms,
-// FP16 1.27 -> 1.04 ms; 128^3 FP32 0.336 -> 0.197 ms.  What bounds it now: FP32 the fetch above,
+// Tile.  At most 256 columns: 64 x 4 (or whole rows of up to 96 cells) take four waves, and up to 192
+// ring columns two or three more; 6 or 7 waves of up to 256 registers and 91 (FP32: 154) KiB of LDS
+// are one block per CU.  Every x-row of a tile also touches the 128-byte lines of its two ring
+// cells, which are whole lines of the neighbouring tiles: they are cheap only while both blocks
+// are at the same plane and the line is in their XCD's L2 (tiles of one XCD are a contiguous
+// patch).  512^3 FP32, array fetched over its size per pass: 32 x 8 tiles 1.99x, 64 x 4 tiles
+// 1.84x, with non-temporal stores, which keep the written planes from pushing those lines out,
+// 1.46x.  The next plane's loads are issued before the second collision: 14.5 -> 13.9 ms per update
+// (same array), 16-bit 10.9 -> 8.4.
+// Measured on MI355X per update, single updates -> pairs: 512^3 FP32 17.5 -> 10.9 ms on a fast
+// array, 20.8 -> 13.7 ms on a plain one; FP16 10.5 -> 8.0 ms (plain); 256^3 FP32 2.60 -> 1.50 ms,
+// FP16 1.27 -> 0.96 ms; 128^3 FP32 0.336 -> 0.188 ms.  What bounds it now: FP32 the fetch above,
 // 16-bit the vector units (7 + 4 wave collisions per 256 cells, 4.4 of 7.3 us a plane).
 #include <algorithm>
 #include <type_traits>
@@ -40,10 +40,11 @@
 
 namespace cnsf {
 
-constexpr int PTX = 64, PTY = 4;              // interior columns of a tile along x and y
-constexpr int PNI = PTX * PTY;                // interior threads
-constexpr int PNR = 2 * PTX + 2 * PTY;        // ring threads
-constexpr int PNT = PNI + (PNR + 63) / 64 * 64;
+constexpr int PNI = 256;          // interior threads: tiles of at most as many columns
+constexpr int PNR = 192;          // ring threads at most
+
+// Ring columns of tiles of tx x ty: a tile as wide as the lattice has its neighbours along x inside.
+__host__ __device__ inline int ring_columns(int tx, int ty, int nx) { return 2 * tx + (tx == nx ? 0 : 2 * ty); }
 
 // Where a level of the lattice is stored: planes z < split in `scr` (cell index as in the
 // lattice), the others in `arr`, split planes further down than in the lattice.
@@ -84,13 +85,13 @@ __device__ inline typename Store<ST>::T load_code(__amdgpu_buffer_rsrc_t r, uint
   }
 }
 
-constexpr int AUX_NT = 2;   // non-temporal
-template <int ST>
-__device__ inline void store_nt(__amdgpu_buffer_rsrc_t r, uint32_t off, float v) {
+template <int ST, bool NT>
+__device__ inline void store_pop(__amdgpu_buffer_rsrc_t r, uint32_t off, float v) {
+  constexpr int AUX = NT ? 2 : 0;   // 2: non-temporal
   if constexpr (ST == 0) {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, (int)off, 0, AUX_NT);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, (int)off, 0, AUX);
   } else {
-    __builtin_amdgcn_raw_buffer_store_b16((short)Store<ST>::enc(v), r, (int)off, 0, AUX_NT);
+    __builtin_amdgcn_raw_buffer_store_b16((short)Store<ST>::enc(v), r, (int)off, 0, AUX);
   }
 }
 
@@ -110,13 +111,13 @@ __device__ inline float decode(const Codec& cd, int k, typename Store<ST>::T c) 
 // One block: planes [za, zb) of one tile, za - 1 and zb being read too.  Planes of one launch:
 // [z_lo, z_hi), `chunk` per block.  Plane wrap_z (one past an end) is read from `wrap`, the
 // links to plane over_z are written to `over`.
-template <int ST, bool SC>
-__global__ void __launch_bounds__(PNT, 2)
+template <int ST, bool SC, bool NT>
+__global__ void __launch_bounds__(PNI + PNR, 2)
 k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T> dst, const Geom g, const Phys ph,
-       const Codec cd, int z_lo, int z_hi, int chunk, int ntx, int ncol, const typename Store<ST>::T* __restrict__ wrap,
+       const Codec cd, int z_lo, int z_hi, int chunk, int tx, int ty, int ntx, int ncol, const typename Store<ST>::T* __restrict__ wrap,
        int wrap_z, typename Store<ST>::T* __restrict__ over, int over_z) {
   using T = typename Store<ST>::T;
-  constexpr int NI = PNI, TY = PTY, PF = ST == 0 ? 6 : 7;   // components fetched ahead: as many as fit 256 VGPRs
+  constexpr int NI = PNI, PF = ST == 0 ? 5 : 7;   // components fetched ahead: as many as fit 256 VGPRs
   __shared__ T xl[2][NC * 4 * NI];   // links along x and y of the last two planes collided, by destination cell
   // links kept by their own thread: rest links (the last RB planes, by z mod RB) and +z links
   // (the last UB planes, by z mod UB).  16-bit links leave room to store a plane's own while the
@@ -128,8 +129,9 @@ k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T
   const uint32_t nb = gridDim.x, per = nb / 8u, rem = nb % 8u, xj = blockIdx.x & 7u, xq = blockIdx.x >> 3;
   const uint32_t t = xj * per + (xj < rem ? xj : rem) + xq;
   const int ch = (int)(t / (uint32_t)ncol), col = (int)(t % (uint32_t)ncol);
-  const int x0 = (col % ntx) * PTX, y0 = (col / ntx) * TY;
-  const int w = min(PTX, (int)g.nx - x0), h = min(TY, (int)g.ny - y0);
+  const int x0 = (col % ntx) * tx, y0 = (col / ntx) * ty;
+  const int w = min(tx, (int)g.nx - x0), h = min(ty, (int)g.ny - y0);
+  const bool row = tx == (int)g.nx;   // whole rows: the links along x stay in the tile
   const int za = z_lo + ch * chunk, zb = min(z_hi, za + chunk);
 
   const int tid = (int)threadIdx.x;
@@ -137,16 +139,16 @@ k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T
   int lx, ly, rdir = 0, rdst = 0;   // tile coordinates; ring threads: link they hand in and its destination
   bool live;
   if (inner) {
-    lx = tid % PTX;
-    ly = tid / PTX;
+    lx = tid % tx;
+    ly = tid / tx;
     live = lx < w && ly < h;
   } else {
     const int r = tid - NI;
-    if (r < PTX) { lx = r; ly = -1; rdir = 2; rdst = r; live = r < w; }
-    else if (r < 2 * PTX) { lx = r - PTX; ly = h; rdir = 3; rdst = (h - 1) * PTX + lx; live = lx < w; }
-    else if (r < 2 * PTX + TY) { lx = -1; ly = r - 2 * PTX; rdir = 0; rdst = ly * PTX; live = ly < h; }
-    else { lx = w; ly = r - 2 * PTX - TY; rdir = 1; rdst = ly * PTX + w - 1; live = ly < h; }
-    if (r >= PNR) live = false;
+    if (r < tx) { lx = r; ly = -1; rdir = 2; rdst = r; live = r < w; }
+    else if (r < 2 * tx) { lx = r - tx; ly = h; rdir = 3; rdst = (h - 1) * tx + lx; live = lx < w; }
+    else if (r < 2 * tx + ty) { lx = -1; ly = r - 2 * tx; rdir = 0; rdst = ly * tx; live = ly < h; }
+    else { lx = w; ly = r - 2 * tx - ty; rdir = 1; rdst = ly * tx + w - 1; live = ly < h; }
+    if (r >= ring_columns(tx, ty, (int)g.nx)) live = false;
   }
   int gx = x0 + lx, gy = y0 + ly;
   gx = gx < 0 ? gx + (int)g.nx : (gx >= (int)g.nx ? gx - (int)g.nx : gx);
@@ -157,6 +159,7 @@ k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T
   const uint32_t cxp = gx == (int)g.nx - 1 ? rowx : cxy + 1u, cxm = gx == 0 ? cxy + (g.nx - 1u) : cxy - 1u;
   const uint32_t cyp = gy == (int)g.ny - 1 ? (uint32_t)gx : cxy + g.nx;
   const uint32_t cym = gy == 0 ? cxy + (g.nxy - g.nx) : cxy - g.nx;
+  const int xp = lx + 1 < w ? 1 : 1 - w, xm = lx > 0 ? -1 : w - 1;   // threads of the neighbours along x
   constexpr uint32_t DEAD = 0xFFFF0000u;   // beyond every region: loads give 0, stores are dropped
 
   T c[NC][NV];   // stored codes of the next plane, in flight
@@ -220,18 +223,18 @@ k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T
     if (links) {
       if (inner) {
         T* X = xw + tid;
-        if (live && lx + 1 < w)
+        if (live && (lx + 1 < w || row))
 #pragma unroll
-          for (int k = 0; k < NC; ++k) X[(k * 4 + 0) * NI + 1] = encode<ST, SC>(cd, k, f[k][1]);
-        if (live && lx > 0)
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 0) * NI + xp] = encode<ST, SC>(cd, k, f[k][1]);
+        if (live && (lx > 0 || row))
 #pragma unroll
-          for (int k = 0; k < NC; ++k) X[(k * 4 + 1) * NI - 1] = encode<ST, SC>(cd, k, f[k][2]);
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 1) * NI + xm] = encode<ST, SC>(cd, k, f[k][2]);
         if (live && ly + 1 < h)
 #pragma unroll
-          for (int k = 0; k < NC; ++k) X[(k * 4 + 2) * NI + PTX] = encode<ST, SC>(cd, k, f[k][3]);
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 2) * NI + tx] = encode<ST, SC>(cd, k, f[k][3]);
         if (live && ly > 0)
 #pragma unroll
-          for (int k = 0; k < NC; ++k) X[(k * 4 + 3) * NI - PTX] = encode<ST, SC>(cd, k, f[k][4]);
+          for (int k = 0; k < NC; ++k) X[(k * 4 + 3) * NI - tx] = encode<ST, SC>(cd, k, f[k][4]);
       } else if (live) {
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
@@ -300,7 +303,7 @@ k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T
         for (int i = 0; i < NV; ++i) {
           const int j = i < 5 ? 0 : i - 4;
           if (ST != 0 && SC) e[i] *= cd.inv_scale[k];
-          store_nt<ST>(region_rsrc(base[j], cs[j], k), o[i], e[i]);
+          store_pop<ST, NT>(region_rsrc(base[j], cs[j], k), o[i], e[i]);
         }
       };
       finish(std::integral_constant<int, 0>{});
@@ -362,56 +365,62 @@ size_t pair_workspace_bytes(const Geom& g, int storage, int split) {
 // How to cut a lattice, and whether two updates in one pass are faster than two single ones.
 // A launch takes rounds x (planes per block + 3) plane times: rounds are its blocks over the CUs,
 // a block reads one plane more at either end and needs about one plane time to start.  Measured
-// plane times (us, TGV boxes of 24^3 to 512^3): FP32 11.0 with full tiles and rows of whole
-// 128-byte lines (10.1-11.1), shorter as fewer of the tile's columns exist, about 4 more when a
-// row starts inside a 64-byte sector (13 at 150^3 and 200^3), 7.2 when the lattice fits the
-// 256 MB last-level cache; 16-bit 7.7 (7.3-8.1) and 2.4 more with rows of partial lines.  Single
-// updates (ns per cell): FP32 0.155 (0.12 in cache), 16-bit 0.077 (0.072).  Pairs must win by 5%:
-// taken at 64^3 FP32 (25 against 31 us per update), 96^3 (94 / 132), 128^3 (193 / 336; 16-bit
-// 139 / 163), 192^3 16-bit (469 / 553); left at 80^3 FP32 (70 / 62), 160^3 and 224^3 16-bit
-// (both equal).
+// plane times (us, TGV boxes of 32^3 to 512^3): FP32 11.0 with full tiles and rows of whole
+// 128-byte lines (9.6-11.2), shorter as fewer of the tile's columns exist, about 2.5 more with
+// rows of partial lines, 6.6-8.2 when the lattice fits the 256 MB last-level cache; 16-bit 7.3
+// (7.0-7.4) and one or two more with rows of partial lines.  Single updates (ns per cell): FP32
+// 0.155 (0.12 in cache), 16-bit 0.077 (0.072).  Pairs must win by 5%.  Taken (us per update, single
+// / pairs): FP32 64^3 31 / 23, 80^3 62 / 49, 96^3 132 / 79, 100^3 173 / 133, 128^3 336 / 188, 150^3
+// 578 / 470; 16-bit 128^3 163 / 123, 192^3 552 / 450, 240^3 1118 / 972.  Left: FP32 48^3 and 16-bit
+// 64^3 (equal), 16-bit 96^3 60 / 73, 200^3 647 / 713, 272^3 1624 / 1759.
+static double plane_us(int storage, int nx, double columns, bool cached) {
+  const double fill = columns / PNI;
+  const int row = nx * (storage == 0 ? 4 : 2);
+  if (storage == 0) return cached ? 7.5 : 11.0 * (0.2 + 0.8 * fill) + (row % 128 ? 2.5 : 0.0);
+  return row % 128 ? 7.3 * (0.5 + 0.5 * fill) + (row % 32 ? 2.0 : 1.0) : 7.3;
+}
+
 bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out) {
   if (g.bc_x != 0) return false;
   const size_t e = storage == 0 ? 4 : 2;
   if (g.cstride * e > 0xFFFF0000ull) return false;   // dead lanes use offsets from there on
-  const int nz = (int)g.nz;
-  const int ncol = (int)((g.nx + PTX - 1) / PTX * ((g.ny + PTY - 1) / PTY));
+  const int nz = (int)g.nz, nx = (int)g.nx, ny = (int)g.ny;
   int m = 1;   // planes that hold whole slot groups
   while (m < (int)SLOT_GROUP && (uint64_t)m * g.nxy % SLOT_GROUP) m *= 2;
-  double best = 1e300;
-  auto consider = [&](int split, int slab) {
-    if (pair_workspace_bytes(g, storage, split) > budget) return;
-    const int nslab = (nz + slab - 1) / slab;
-    for (int c = 1; c <= std::min(slab, 64); ++c) {
-      const int h = (slab + c - 1) / c;
-      const int rounds = (ncol * ((slab + h - 1) / h) + cus - 1) / cus;
-      const double t = (double)nslab * rounds * (h + 3);
-      if (t < best) {
-        best = t;
-        out->split = split;
-        out->slab = slab;
-        out->chunk = h;
-      }
-    }
-  };
-  consider(nz, nz);
-  for (int n = 2; n * 4 <= nz && nz / n >= 4; ++n) {
-    const int slab = (nz + n - 1) / n, split = (slab + 2 + m - 1) / m * m;
-    if (split + 2 <= nz) consider(split, slab);
-  }
-  if (best > 1e299) return false;
   const bool cached = (double)NP * e * g.ncells <= 256e6;
-  const size_t row = g.nx * e;
-  const double fill = (double)g.nxy / ((double)ncol * PNI);
-  double plane, cell;
-  if (storage == 0) {
-    plane = cached ? 7.2 : 11.0 * (0.2 + 0.8 * fill) + (row % 64 ? 4.0 : (row % 128 ? 2.0 : 0.0));
-    cell = cached ? 0.12 : 0.155;
-  } else {
-    plane = row % 128 ? 7.6 * (0.4 + 0.6 * fill) + 2.4 : 7.7;
-    cell = cached ? 0.072 : 0.077;
+  double best = 1e300;
+  // whole rows up to 96 cells, else tiles that start on line boundaries (equal cuts lose: 112^3 FP32
+  // 56-wide 196 us per update, 64-wide 154; 320^3 54-wide 5.7 ms, 64-wide 3.4)
+  for (const int tx : {nx, 64}) {
+    if (tx > 96 || (tx == 64 && nx < 64)) continue;
+    const int ntx = (nx + tx - 1) / tx;
+    int ty = std::min(PNI / tx, ny);
+    while (ty > 1 && ring_columns(tx, ty, nx) > PNR) --ty;
+    if (ring_columns(tx, ty, nx) > PNR) continue;
+    ty = (ny + (ny + ty - 1) / ty - 1) / ((ny + ty - 1) / ty);
+    const int ncol = ntx * ((ny + ty - 1) / ty);
+    const double plane = plane_us(storage, nx, (double)g.nxy / ncol, cached);
+    auto consider = [&](int split, int slab) {
+      if (pair_workspace_bytes(g, storage, split) > budget) return;
+      const int nslab = (nz + slab - 1) / slab;
+      for (int c = 1; c <= std::min(slab, 64); ++c) {
+        const int h = (slab + c - 1) / c;
+        const int rounds = (ncol * ((slab + h - 1) / h) + cus - 1) / cus;
+        const double t = (double)nslab * rounds * (h + 3) * plane;
+        if (t < best) {
+          best = t;
+          *out = PairPlan{split, slab, h, tx, ty};
+        }
+      }
+    };
+    consider(nz, nz);
+    for (int n = 2; n * 4 <= nz && nz / n >= 4; ++n) {
+      const int slab = (nz + n - 1) / n, split = (slab + 2 + m - 1) / m * m;
+      if (split + 2 <= nz) consider(split, slab);
+    }
   }
-  return 1.05 * best * plane < 2e-3 * cell * g.ncells;
+  const double cell = storage == 0 ? (cached ? 0.12 : 0.155) : (cached ? 0.072 : 0.077);
+  return 1.05 * best < 2e-3 * cell * g.ncells;
 }
 
 template <int ST, bool SC>
@@ -425,6 +434,10 @@ static hipError_t launch_pair_t(void* pop, void* ws, const Geom& g, const Phys& 
   T* over = wrap + (uint64_t)NP * groups(g.nxy);
   const Place<T> home{(T*)pop, scr, g.cstride, cs_scr, 0}, moved{(T*)pop, scr, g.cstride, cs_scr, pl.split};
   const Place<T> src = back ? moved : home, dst = back ? home : moved;
+  // non-temporal stores from arrays of 32 GB on: 512^3 FP32 10.9 ms per update against 12.8 with
+  // ordinary ones, 384^3 and 320^3 the same with both, rows of partial lines and 16-bit codes slower
+  // (100^3 164 against 133 us, 256^3 FP16 1057 against 955): the partial lines no longer meet in L2
+  const bool nt = (double)NP * sizeof(T) * g.ncells >= 32e9;
   const int nz = (int)g.nz, none = -1000000;
   const int wrap_z = whole ? none : (back ? -1 : nz), over_z = whole ? none : (back ? nz : -1);
   auto cell = [&](const Place<T>& p, int z, T*& b, uint64_t& cs) {
@@ -439,14 +452,18 @@ static hipError_t launch_pair_t(void* pop, void* ws, const Geom& g, const Phys& 
     const uint32_t c0 = cell(src, back ? nz - 1 : 0, b, cs);
     hipLaunchKernelGGL(k_plane_save<T>, pg, dim3(256), 0, s, (const T*)b, cs, c0, g.nxy, wrap, (uint64_t)NV * groups(g.nxy));
   }
-  const int ntx = ((int)g.nx + PTX - 1) / PTX, ncol = ntx * (((int)g.ny + PTY - 1) / PTY);
+  const int ntx = ((int)g.nx + pl.tx - 1) / pl.tx, ncol = ntx * (((int)g.ny + pl.ty - 1) / pl.ty);
+  const int threads = PNI + (ring_columns(pl.tx, pl.ty, (int)g.nx) + 63) / 64 * 64;
+  auto kernel = k_pair<ST, SC, false>;
+  if constexpr (ST == 0)
+    if (nt) kernel = k_pair<ST, SC, true>;
   const int nslab = (nz + pl.slab - 1) / pl.slab;
   for (int j = 0; j < nslab; ++j) {
     const int q = back ? nslab - 1 - j : j;
     const int z0 = q * pl.slab, z1 = std::min(nz, z0 + pl.slab);
     const int nch = (z1 - z0 + pl.chunk - 1) / pl.chunk;
-    hipLaunchKernelGGL((k_pair<ST, SC>), dim3(ncol * nch), dim3(PNT), 0, s, src, dst, g, ph, cd, z0, z1,
-                       pl.chunk, ntx, ncol, (const T*)wrap, wrap_z, over, over_z);
+    hipLaunchKernelGGL(kernel, dim3(ncol * nch), dim3(threads), 0, s, src, dst, g, ph, cd, z0, z1, pl.chunk, pl.tx,
+                       pl.ty, ntx, ncol, (const T*)wrap, wrap_z, over, over_z);
   }
   if (!whole) {
     T* b;
