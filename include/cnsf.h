@@ -185,7 +185,10 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * bit, when n >= 4 (5 from an odd level).  The first such call allocates a
  * workspace, kept until cnsf_destroy: the array's size up to 2 GiB, an eighth
  * of the array beyond, at most an eighth of the free device memory; without it
- * (or after cnsf_set_launch) the lattice stays on single updates.
+ * (or after cnsf_set_launch) the lattice stays on single updates.  Thin lattices
+ * (ny * nz of a few tens of cells at most: tubes, channels, columns) likewise
+ * make several updates per launch, with a workspace of the array's size unless
+ * they have no more than 256 cells.
  * CNSF_E_DEVICE if a launch fails. */
 int cnsf_step(cnsf_lattice* lat, int64_t n);
 

@@ -243,6 +243,10 @@ struct cnsf_lattice {
   void* pair_ws = nullptr;
   PairPlan pair;
   bool pair_decided = false;
+  // several updates per launch: second array (unless one window holds the lattice) and windows
+  void* tube_ws = nullptr;
+  TubePlan tube;
+  bool tube_decided = false;
   bool own_launch = false;               // the caller chose the launch shape of the update
 };
 
@@ -292,6 +296,48 @@ bool pair_ready(cnsf_lattice* L, bool may_alloc) {
     L->pair_ws = nullptr;
   }
   return L->pair_ws != nullptr;
+}
+
+// Whether `L` advances by windows of several updates (tube.hip); decides and allocates like pair_ready.
+bool tube_ready(cnsf_lattice* L, bool may_alloc) {
+  if (L->own_launch) return false;
+  if (!L->tube_decided && may_alloc) {
+    L->tube_decided = true;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) cus = 0;
+    if (cus > 0 && tube_plan(L->g, L->p.storage, cus, &L->tube) && L->tube.xw != (int)L->g.nx &&
+        hipMalloc(&L->tube_ws, L->bytes) != hipSuccess) {
+      (void)hipGetLastError();   // single updates then
+      L->tube_ws = nullptr;
+    }
+  }
+  return L->tube.xw == (int)L->g.nx || L->tube_ws != nullptr;
+}
+
+// Up to n updates from an even level by windows (an even number); *left: n less what was enqueued.
+hipError_t tube_steps(cnsf_lattice* L, int64_t n, int64_t* left) {
+  constexpr int64_t WHOLE_STEPS = 4096;   // updates of one launch of a lattice that fits one window
+  hipError_t e = hipSuccess;
+  if (L->tube.xw == (int)L->g.nx) {
+    *left = n & 1;
+    for (n -= *left; n > 0 && e == hipSuccess; n -= std::min(n, WHOLE_STEPS))
+      e = launch_tube(L->p.storage, L->pop, L->pop, L->g, L->ph, L->cd, L->tube.xw, (int)std::min(n, WHOLE_STEPS), L->stream);
+    return e;
+  }
+  // an even number of launches of even numbers of updates, as equal as they can be
+  int64_t units = n / 2;
+  const int64_t most = L->tube.steps / 2;
+  int64_t launches = (units + most - 1) / most;
+  launches += launches & 1;
+  if (launches > units) units = launches = units & ~(int64_t)1;   // two updates a launch, an odd number of launches
+  *left = n - 2 * units;
+  for (int64_t j = 0; j < launches && e == hipSuccess; ++j) {
+    const int64_t u = units * (j + 1) / launches - units * j / launches;
+    void* a = j & 1 ? L->tube_ws : L->pop;
+    void* b = j & 1 ? L->pop : L->tube_ws;
+    e = launch_tube(L->p.storage, a, b, L->g, L->ph, L->cd, L->tube.xw, (int)(2 * u), L->stream);
+  }
+  return e;
 }
 
 // GRAPH_STEPS updates from even parity, captured on the lattice's own capture
@@ -402,6 +448,7 @@ int cnsf_destroy(cnsf_lattice* L) {
   if (L->step_partials) (void)hipFree(L->step_partials);
   if (L->dresult2) (void)hipFree(L->dresult2);
   if (L->pair_ws) (void)hipFree(L->pair_ws);
+  if (L->tube_ws) (void)hipFree(L->tube_ws);
   drop_graph(L);
   if (L->gstream) (void)hipStreamDestroy(L->gstream);
   delete L;
@@ -464,9 +511,9 @@ static int set_state_impl(cnsf_lattice* L, const double* Q, int32_t z0, int32_t 
   return CNSF_OK;
 }
 
-// n >= 0 updates; may_pair: by paired passes where they are faster, may_alloc: their workspace
-// may be allocated now.
-static int step_impl(cnsf_lattice* L, int64_t n, bool may_pair, bool may_alloc) {
+// n >= 0 updates; may_multi: several per pass where that is faster, may_alloc: the workspace of
+// those may be allocated now.
+static int step_impl(cnsf_lattice* L, int64_t n, bool may_multi, bool may_alloc) {
   (void)hipSetDevice(L->device);
   int64_t left = n;
   hipError_t e = hipSuccess;
@@ -474,7 +521,13 @@ static int step_impl(cnsf_lattice* L, int64_t n, bool may_pair, bool may_alloc) 
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (L->stream) (void)hipStreamIsCapturing(L->stream, &cap);
   const bool plain = cap != hipStreamCaptureStatusNone;
-  if (!plain && may_pair && n - L->parity >= PAIR_STEPS && pair_ready(L, may_alloc)) {
+  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, may_alloc)) {
+    if (L->parity) {
+      e = launch_steps(L, 1, L->stream, L->parity);
+      --left;
+    }
+    if (e == hipSuccess) e = tube_steps(L, left, &left);
+  } else if (!plain && may_multi && n - L->parity >= PAIR_STEPS && pair_ready(L, may_alloc)) {
     if (L->parity) {
       e = launch_steps(L, 1, L->stream, L->parity);
       --left;

@@ -42,6 +42,16 @@ size_t pair_workspace_bytes(const Geom& g, int storage, int split);
 hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd,
                        const PairPlan& pl, bool back, hipStream_t s);
 
+// Several updates per launch for thin lattices (tube.hip): planes of a window and the even number
+// of updates per launch.  A window as long as the lattice takes any number, in place.
+struct TubePlan {
+  int xw = 0, steps = 0;
+};
+bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out);
+// `steps` (even) updates of a lattice at an even level, from src to dst (both laid out as the array).
+hipError_t launch_tube(int storage, const void* src, void* dst, const Geom& g, const Phys& ph, const Codec& cd, int xw,
+                       int steps, hipStream_t s);
+
 // Diagnostics: FP64 sums and the spectral dissipation averages.
 struct DiagPartial {
   double mass, mx, my, mz, energy, ek2;  // ek2 = sum rho |u|^2
