@@ -33,8 +33,11 @@ __device__ inline uint32_t xcd_block(uint32_t b, uint32_t nb) {
 // DIAG instances also reduce the Eq. (7) sums of the time level they read
 // (one partial per block, as the diagnostics readout forms them) and, when
 // `fields` is given, write u, v, w, mu for the spectral derivatives.
+//
+// The FP16 diagnostic instance is held to two waves per SIMD (264 registers otherwise, one wave:
+// 256^3 1.62 -> 1.38 ms); the BF16 one fits by itself and loses under the same bound (1.43 -> 3.04).
 template <int ST, int BC, bool SC, int PAR, bool DIAG>
-__global__ void __launch_bounds__(256) k_update(typename Store<ST>::T* __restrict__ pop, const Geom g, const Phys ph,
+__global__ void __launch_bounds__(256, DIAG && ST == 1 && !SC ? 2 : 1) k_update(typename Store<ST>::T* __restrict__ pop, const Geom g, const Phys ph,
                                                 const Codec cd, uint32_t tile, uint32_t ntiles, int remap,
                                                 const PhysD phd, DiagPartial* __restrict__ partials,
                                                 double* __restrict__ fields) {
@@ -115,25 +118,60 @@ __global__ void k_init(typename Store<ST>::T* __restrict__ pop, const double* __
   }
 }
 
+// Stored codes of all populations of a cell, apart from their arithmetic: a readout has nothing to
+// do but wait for them, and scaled and summed as they were loaded seven 2-byte loads per wave were
+// in flight, a component's (moments of 256^3 FP16 2.47 ms, 2.1 TB/s). Now the compiler keeps some
+// forty ahead: 0.97 ms, 5.3 TB/s (FP32 as before, 1.62 ms, 5.2 TB/s).
+template <int ST>
+__device__ inline void load_codes(const typename Store<ST>::T* __restrict__ pop, const Geom& g, const uint32_t off[NV],
+                                  typename Store<ST>::T c[NC][NV]) {
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const __amdgpu_buffer_rsrc_t rs = component_rsrc<ST>(pop, g, k);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      if constexpr (ST == 0) c[k][i] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off[i], 0, 0));
+      else c[k][i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)off[i], 0, 0);
+    }
+  }
+}
+
+// Q_k = Q_ref,k + sum_i g_{k,i} of the current time level (FP64 sums in slot order; R: the type in
+// which a code is scaled), ends as in gather.
+template <int ST, int BC, typename R>
+__device__ inline void cell_moments(const typename Store<ST>::T c[NC][NV], const Geom& g, const Codec& cd, const Nbr& n,
+                                    int parity, double Q[NC]) {
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      R v = (R)Store<ST>::dec(c[k][i]);
+      if (ST != 0) v *= (R)cd.scale[k];
+      if (crossed_end<BC>(g, n, parity, i)) {
+        if (BC == 1 && x_odd(k)) v = -v;
+        if (BC == 2) v = (R)(i == 1 ? g.dev_left[k] : g.dev_right[k]);
+      }
+      s += (double)v;
+    }
+    Q[k] = q_ref<double>(cd, k) + s;
+  }
+}
+
 // rho, u (3), p, T of the current time level (FP64, from the FP64 moments).
 template <int ST, int BC>
-__global__ void k_primitives(const typename Store<ST>::T* __restrict__ pop, double* __restrict__ out, const Geom g,
-                             const Codec cd, const PhysD ph, int parity, uint32_t cell0, uint32_t nslab) {
+__global__ void __launch_bounds__(256) k_primitives(const typename Store<ST>::T* __restrict__ pop,
+                                                    double* __restrict__ out, const Geom g, const Codec cd,
+                                                    const PhysD ph, int parity, uint32_t cell0, uint32_t nslab) {
   const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= nslab) return;
   const Nbr n = neighbours(cell0 + j, g);
   uint32_t off[NV];
   stream_offsets<ST, BC>(g, n, parity, off);
-  float gf[NC][NV];
-  gather<ST, BC, true, float>(pop, g, cd, n, parity, off, gf);
+  typename Store<ST>::T c[NC][NV];
+  load_codes<ST>(pop, g, off, c);
   double Q[NC];
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) s += (double)gf[k][i];
-    Q[k] = q_ref<double>(cd, k) + s;
-  }
+  cell_moments<ST, BC, float>(c, g, cd, n, parity, Q);
   const Prim<double> P = primitives<double>(Q, ph);
   const double v[6] = {P.rho, P.u[0], P.u[1], P.u[2], P.p, P.T};
 #pragma unroll
@@ -142,22 +180,20 @@ __global__ void k_primitives(const typename Store<ST>::T* __restrict__ pop, doub
 
 // Q_k = sum_i f_{k,i} of the current time level (FP64 accumulation).
 template <int ST, int BC>
-__global__ void k_moments(const typename Store<ST>::T* __restrict__ pop, double* __restrict__ out, const Geom g,
-                          const Codec cd, int parity, uint32_t cell0, uint32_t nslab) {
+__global__ void __launch_bounds__(256) k_moments(const typename Store<ST>::T* __restrict__ pop, double* __restrict__ out,
+                                                 const Geom g, const Codec cd, int parity, uint32_t cell0,
+                                                 uint32_t nslab) {
   const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= nslab) return;
   const Nbr n = neighbours(cell0 + j, g);
   uint32_t off[NV];
   stream_offsets<ST, BC>(g, n, parity, off);
-  double gv[NC][NV];
-  gather<ST, BC, true, double>(pop, g, cd, n, parity, off, gv);
+  typename Store<ST>::T c[NC][NV];
+  load_codes<ST>(pop, g, off, c);
+  double Q[NC];
+  cell_moments<ST, BC, double>(c, g, cd, n, parity, Q);
 #pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) s += gv[k][i];
-    out[(uint64_t)k * nslab + j] = q_ref<double>(cd, k) + s;
-  }
+  for (int k = 0; k < NC; ++k) out[(uint64_t)k * nslab + j] = Q[k];
 }
 
 // Plain copy, 4 x 16 bytes in flight per thread per iteration, non-temporal
