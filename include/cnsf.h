@@ -308,13 +308,18 @@ int cnsf_batch_destroy(cnsf_batch* b);
 /* Member j's initial state (as cnsf_set_state, whole lattice). */
 int cnsf_batch_set_state(cnsf_batch* b, int32_t j, const double* Q, int32_t where);
 /* Advance every member by n steps.  mode 0: one launch per step over all
- * members; mode 1: the same launches replayed from a HIP graph of
- * `graph_steps` steps (captured on first use); mode 2: one launch per member
- * per step (the sequential baseline). */
+ * members; mode 1: two steps per pass over memory where that is faster (the
+ * first such call takes a second array of the batch's size, if that is within
+ * 32 GiB and an eighth of the free device memory, and keeps it until
+ * cnsf_batch_destroy; the stored populations are the same bit for bit), else
+ * mode 0's launches replayed from a HIP graph of `graph_steps` steps (captured
+ * on first use); mode 2: one launch per member per step (the sequential
+ * baseline).  While the stream is being captured, mode 1 records no paired
+ * passes. */
 int cnsf_batch_step(cnsf_batch* b, int64_t n, int32_t mode);
 /* Member j's moments (as cnsf_get_moments, whole lattice). */
 int cnsf_batch_get_moments(cnsf_batch* b, int32_t j, double* out, int32_t where);
-/* Launch shape of the batched kernel: threads per block (64..256, multiple of
+/* Launch shape of the batched single-step kernel: threads per block (64..256, multiple of
  * 64), cells per tile (multiple of block), persistent grid size in blocks
  * (0: one block per tile), and the number of steps captured per graph. */
 int cnsf_batch_set_launch(cnsf_batch* b, int32_t block, int32_t tile, int32_t grid, int32_t graph_steps);

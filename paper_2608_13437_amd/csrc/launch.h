@@ -42,6 +42,27 @@ size_t pair_workspace_bytes(const Geom& g, int storage, int split);
 hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd,
                        const PairPlan& pl, bool back, hipStream_t s);
 
+// One member of a batch in the device table, and its cut for paired passes (second array: member
+// after member, each laid out like a lattice of its own).
+struct Member {
+  Geom g;
+  Phys ph;
+  Codec cd;
+  uint64_t pop_offset;  // elements from the batch base
+  uint32_t tile0;       // first tile of this member
+  uint32_t ntiles;
+};
+struct PairMember {
+  uint32_t block0;
+  int tx, ty, ntx, ncol, chunk;
+  uint64_t offset, cstride;
+};
+bool pair_batch_plan(const Member* m, int n, int storage, int cus, PairMember* out, uint32_t* blocks, int* threads,
+                     uint64_t* elements);
+hipError_t launch_pair_batch(int storage, bool scaled, void* home, void* second, const Member* members,
+                             const PairMember* pm, const uint16_t* block_member, uint32_t blocks, int threads, bool back,
+                             hipStream_t s);
+
 // Several updates per launch for thin lattices (tube.hip): planes of a window and the even number
 // of updates per launch.  A window as long as the lattice takes any number, in place.
 struct TubePlan {

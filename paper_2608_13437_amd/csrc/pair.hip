@@ -108,31 +108,35 @@ __device__ inline float decode(const Codec& cd, int k, typename Store<ST>::T c) 
   return v;
 }
 
-// One block: planes [za, zb) of one tile, za - 1 and zb being read too.  Planes of one launch:
-// [z_lo, z_hi), `chunk` per block.  Plane wrap_z (one past an end) is read from `wrap`, the
-// links to plane over_z are written to `over`.
+// LDS of a block: links along x and y of the last two planes collided, by destination cell, and
+// links kept by their own thread: rest links (the last RB planes, by z mod RB) and +z links (the
+// last UB planes, by z mod UB).  16-bit links leave room to store a plane's own while the older ones
+// are still needed; FP32 links wait in registers until those are consumed.
+template <int ST>
+struct PairLds {
+  using T = typename Store<ST>::T;
+  static constexpr bool EARLY = ST != 0;
+  static constexpr int RB = EARLY ? 2 : 1, UB = EARLY ? 3 : 2;
+  T xl[2][NC * 4 * PNI];
+  T zl[NC * (RB + UB) * PNI];
+};
+
+// One block: planes [za, zb) of the tile at (x0, y0) of tiles tx x ty, za - 1 and zb being read too.
+// Plane wrap_z (one past an end) is read from `wrap`, the links to plane over_z are written to `over`.
 template <int ST, bool SC, bool NT>
-__global__ void __launch_bounds__(PNI + PNR, 2)
-k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T> dst, const Geom g, const Phys ph,
-       const Codec cd, int z_lo, int z_hi, int chunk, int tx, int ty, int ntx, int ncol, const typename Store<ST>::T* __restrict__ wrap,
-       int wrap_z, typename Store<ST>::T* __restrict__ over, int over_z) {
+__device__ inline void pair_block(PairLds<ST>& sh, const Place<typename Store<ST>::T> src,
+                                  const Place<typename Store<ST>::T> dst, const Geom& g, const Phys& ph, const Codec& cd,
+                                  int za, int zb, int x0, int y0, int tx, int ty,
+                                  const typename Store<ST>::T* __restrict__ wrap, int wrap_z,
+                                  typename Store<ST>::T* __restrict__ over, int over_z) {
   using T = typename Store<ST>::T;
   constexpr int NI = PNI, PF = ST == 0 ? 5 : 7;   // components fetched ahead: as many as fit 256 VGPRs
-  __shared__ T xl[2][NC * 4 * NI];   // links along x and y of the last two planes collided, by destination cell
-  // links kept by their own thread: rest links (the last RB planes, by z mod RB) and +z links
-  // (the last UB planes, by z mod UB).  16-bit links leave room to store a plane's own while the
-  // older ones are still needed; FP32 links wait in registers until those are consumed.
-  constexpr bool EARLY = ST != 0;
-  constexpr int RB = EARLY ? 2 : 1, UB = EARLY ? 3 : 2;
-  __shared__ T zl[NC * (RB + UB) * NI];
-  // tile: XCD j takes a contiguous span of tiles of one chunk after the other
-  const uint32_t nb = gridDim.x, per = nb / 8u, rem = nb % 8u, xj = blockIdx.x & 7u, xq = blockIdx.x >> 3;
-  const uint32_t t = xj * per + (xj < rem ? xj : rem) + xq;
-  const int ch = (int)(t / (uint32_t)ncol), col = (int)(t % (uint32_t)ncol);
-  const int x0 = (col % ntx) * tx, y0 = (col / ntx) * ty;
+  constexpr bool EARLY = PairLds<ST>::EARLY;
+  constexpr int RB = PairLds<ST>::RB, UB = PairLds<ST>::UB;
+  auto& xl = sh.xl;
+  auto& zl = sh.zl;
   const int w = min(tx, (int)g.nx - x0), h = min(ty, (int)g.ny - y0);
   const bool row = tx == (int)g.nx;   // whole rows: the links along x stay in the tile
-  const int za = z_lo + ch * chunk, zb = min(z_hi, za + chunk);
 
   const int tid = (int)threadIdx.x;
   const bool inner = __builtin_amdgcn_readfirstlane(tid) < NI;
@@ -332,6 +336,53 @@ k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T
   }
 }
 
+// Position of block b among nb when XCD j takes a contiguous span of them.
+__device__ inline uint32_t xcd_span(uint32_t b, uint32_t nb) {
+  const uint32_t per = nb / 8u, rem = nb % 8u, j = b & 7u;
+  return j * per + (j < rem ? j : rem) + (b >> 3);
+}
+
+// A launch: planes [z_lo, z_hi), `chunk` per block; tiles of one chunk after the other.
+template <int ST, bool SC, bool NT>
+__global__ void __launch_bounds__(PNI + PNR, 2)
+k_pair(const Place<typename Store<ST>::T> src, const Place<typename Store<ST>::T> dst, const Geom g, const Phys ph,
+       const Codec cd, int z_lo, int z_hi, int chunk, int tx, int ty, int ntx, int ncol,
+       const typename Store<ST>::T* __restrict__ wrap, int wrap_z, typename Store<ST>::T* __restrict__ over, int over_z) {
+  __shared__ PairLds<ST> sh;
+  const uint32_t t = xcd_span(blockIdx.x, gridDim.x);
+  const int ch = (int)(t / (uint32_t)ncol), col = (int)(t % (uint32_t)ncol), za = z_lo + ch * chunk;
+  pair_block<ST, SC, NT>(sh, src, dst, g, ph, cd, za, min(z_hi, za + chunk), (col % ntx) * tx, (col / ntx) * ty, tx, ty,
+                         wrap, wrap_z, over, over_z);
+}
+
+// Position of block b when runs of 32 consecutive tiles, one per CU of an XCD, are dealt to the XCDs in
+// turn: a batch's tiles differ in cost, and whole spans would leave XCDs idle.
+__device__ inline uint32_t xcd_deal(uint32_t b, uint32_t nb) {
+  return b < nb / 256u * 256u ? b / 256u * 256u + (b & 7u) * 32u + ((b >> 3) & 31u) : b;
+}
+
+// All members of a batch: from each member's array to its place in the second one, or back.
+template <int ST, bool SC>
+__global__ void __launch_bounds__(PNI + PNR, 2)
+k_pair_batch(typename Store<ST>::T* __restrict__ home, typename Store<ST>::T* __restrict__ second,
+             const Member* __restrict__ members, const PairMember* __restrict__ pm,
+             const uint16_t* __restrict__ block_member, int back) {
+  using T = typename Store<ST>::T;
+  __shared__ PairLds<ST> sh;
+  const uint32_t t = xcd_deal(blockIdx.x, gridDim.x);
+  const uint32_t m = __builtin_amdgcn_readfirstlane(block_member[t]);
+  const Member& M = members[m];
+  const PairMember& P = pm[m];
+  const Geom g = M.g;
+  const int q = (int)(t - P.block0), ch = q / P.ncol, col = q % P.ncol, za = ch * P.chunk;
+  T* const a = home + M.pop_offset;
+  T* const b = second + P.offset;
+  const Place<T> at_home{a, b, g.cstride, P.cstride, 0}, moved{a, b, g.cstride, P.cstride, (int)g.nz};
+  pair_block<ST, SC, false>(sh, back ? moved : at_home, back ? at_home : moved, g, M.ph, M.cd, za,
+                            min((int)g.nz, za + P.chunk), (col % P.ntx) * P.tx, (col / P.ntx) * P.ty, P.tx, P.ty,
+                            (const T*)nullptr, -1000000, (T*)nullptr, -1000000);
+}
+
 // One plane's stored populations, copied aside (98 slots; groups as in the lattice, cell 0 first).
 template <typename T>
 __global__ void __launch_bounds__(256) k_plane_save(const T* __restrict__ base, uint64_t cs, uint32_t cell0, uint32_t nxy,
@@ -362,6 +413,25 @@ size_t pair_workspace_bytes(const Geom& g, int storage, int split) {
   return n * e;
 }
 
+// Rows of a tile of tx columns, 0 if there is no such tile: whole rows up to 96 cells, else tiles that
+// start on line boundaries (equal cuts lose: 112^3 FP32 56-wide 196 us per update, 64-wide 154; 320^3
+// 54-wide 5.7 ms, 64-wide 3.4).
+static int tile_rows(int tx, int nx, int ny) {
+  if (tx > 96 || (tx == 64 && nx < 64)) return 0;
+  int ty = std::min(PNI / tx, ny);
+  while (ty > 1 && ring_columns(tx, ty, nx) > PNR) --ty;
+  if (ring_columns(tx, ty, nx) > PNR) return 0;
+  const int n = (ny + ty - 1) / ty;
+  return (ny + n - 1) / n;
+}
+
+static double plane_us(int storage, int nx, double columns, bool cached) {
+  const double fill = columns / PNI;
+  const int row = nx * (storage == 0 ? 4 : 2);
+  if (storage == 0) return cached ? 7.5 : 11.0 * (0.2 + 0.8 * fill) + (row % 128 ? 2.5 : 0.0);
+  return row % 128 ? 7.3 * (0.5 + 0.5 * fill) + (row % 32 ? 2.0 : 1.0) : 7.3;
+}
+
 // How to cut a lattice, and whether two updates in one pass are faster than two single ones.
 // A launch takes rounds x (planes per block + 3) plane times: rounds are its blocks over the CUs,
 // a block reads one plane more at either end and needs about one plane time to start.  Measured
@@ -373,13 +443,6 @@ size_t pair_workspace_bytes(const Geom& g, int storage, int split) {
 // / pairs): FP32 64^3 31 / 23, 80^3 62 / 49, 96^3 132 / 79, 100^3 173 / 133, 128^3 336 / 188, 150^3
 // 578 / 470; 16-bit 128^3 163 / 123, 192^3 552 / 450, 240^3 1118 / 972.  Left: FP32 48^3 and 16-bit
 // 64^3 (equal), 16-bit 96^3 60 / 73, 200^3 647 / 713, 272^3 1624 / 1759.
-static double plane_us(int storage, int nx, double columns, bool cached) {
-  const double fill = columns / PNI;
-  const int row = nx * (storage == 0 ? 4 : 2);
-  if (storage == 0) return cached ? 7.5 : 11.0 * (0.2 + 0.8 * fill) + (row % 128 ? 2.5 : 0.0);
-  return row % 128 ? 7.3 * (0.5 + 0.5 * fill) + (row % 32 ? 2.0 : 1.0) : 7.3;
-}
-
 bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out) {
   if (g.bc_x != 0) return false;
   const size_t e = storage == 0 ? 4 : 2;
@@ -389,16 +452,10 @@ bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out
   while (m < (int)SLOT_GROUP && (uint64_t)m * g.nxy % SLOT_GROUP) m *= 2;
   const bool cached = (double)NP * e * g.ncells <= 256e6;
   double best = 1e300;
-  // whole rows up to 96 cells, else tiles that start on line boundaries (equal cuts lose: 112^3 FP32
-  // 56-wide 196 us per update, 64-wide 154; 320^3 54-wide 5.7 ms, 64-wide 3.4)
   for (const int tx : {nx, 64}) {
-    if (tx > 96 || (tx == 64 && nx < 64)) continue;
-    const int ntx = (nx + tx - 1) / tx;
-    int ty = std::min(PNI / tx, ny);
-    while (ty > 1 && ring_columns(tx, ty, nx) > PNR) --ty;
-    if (ring_columns(tx, ty, nx) > PNR) continue;
-    ty = (ny + (ny + ty - 1) / ty - 1) / ((ny + ty - 1) / ty);
-    const int ncol = ntx * ((ny + ty - 1) / ty);
+    const int ty = tile_rows(tx, nx, ny);
+    if (!ty) continue;
+    const int ntx = (nx + tx - 1) / tx, ncol = ntx * ((ny + ty - 1) / ty);
     const double plane = plane_us(storage, nx, (double)g.nxy / ncol, cached);
     auto consider = [&](int split, int slab) {
       if (pair_workspace_bytes(g, storage, split) > budget) return;
@@ -480,6 +537,96 @@ hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Ph
   if (storage == 0) return launch_pair_t<0, false>(pop, ws, g, ph, cd, pl, back, s);
   if (storage == 1) return (sc ? launch_pair_t<1, true> : launch_pair_t<1, false>)(pop, ws, g, ph, cd, pl, back, s);
   return (sc ? launch_pair_t<2, true> : launch_pair_t<2, false>)(pop, ws, g, ph, cd, pl, back, s);
+}
+
+// Tiles of every member for blocks of about `height` planes; the blocks' total time and that of the
+// longest one (us), 0 total if some member has no tile.
+static double batch_cut(const Member* m, int n, int storage, int height, PairMember* out, uint32_t* blocks, int* threads,
+                        double* longest) {
+  double total = 0.0;
+  uint64_t off = 0;
+  *blocks = 0;
+  *threads = 0;
+  *longest = 0.0;
+  for (int j = 0; j < n; ++j) {
+    const Geom& g = m[j].g;
+    const int nx = (int)g.nx, ny = (int)g.ny, nz = (int)g.nz;
+    if (nz < 4) return 0.0;   // a block's planes wrap around the end once
+    PairMember& P = out[j];
+    const int c = std::max(1, (nz + height / 2) / height);
+    P.chunk = (nz + c - 1) / c;
+    const int nch = (nz + P.chunk - 1) / P.chunk;
+    double best = 1e300, block = 0.0;
+    for (const int tx : {nx, 64}) {
+      const int ty = tile_rows(tx, nx, ny);
+      if (!ty) continue;
+      const int ntx = (nx + tx - 1) / tx, ncol = ntx * ((ny + ty - 1) / ty);
+      const double us = plane_us(storage, nx, (double)g.nxy / ncol, false) * (P.chunk + 3);
+      if (us * ncol < best) {
+        best = us * ncol;
+        block = us;
+        P.tx = tx;
+        P.ty = ty;
+        P.ntx = ntx;
+        P.ncol = ncol;
+      }
+    }
+    if (best > 1e299) return 0.0;
+    P.block0 = *blocks;
+    P.offset = off;
+    P.cstride = (uint64_t)NV * groups(g.ncells);
+    off += (uint64_t)NC * P.cstride;
+    *blocks += (uint32_t)(P.ncol * nch);
+    *threads = std::max(*threads, PNI + (ring_columns(P.tx, P.ty, nx) + 63) / 64 * 64);
+    total += best * nch;
+    *longest = std::max(*longest, block);
+  }
+  return total;
+}
+
+// Cut of a batch and whether pairs are the faster way.  Higher blocks read fewer planes twice, lower
+// ones end closer together: a pass takes the blocks' time over all CUs (0.77 of it FP32, 0.85 16-bit:
+// the plane times are those of a lattice alone, where every CU is at the same step) and 0.8 of the
+// longest block's.  Single updates (ns per cell): FP32 0.155, 16-bit 0.08.  Measured, single / pairs in
+// ms per update (64 members of 32^3 to 96^3, heights 12 / 16 / 24 / 32 / 48): FP32 3.85 / 2.02, 1.98,
+// 2.04, 2.01, 2.12; FP16 1.87 / 1.68, 1.61, 1.68, 1.64, 1.74; 64 of 64^3 FP16 1.30 / 1.02, 0.99, 0.98,
+// 0.96, 0.94.  Few members: 8 of mixed sizes FP16 0.16 / 0.15, BF16 0.29 / 0.29 and three BF16 0.17 /
+// 0.20 are left to single updates.
+bool pair_batch_plan(const Member* m, int n, int storage, int cus, PairMember* out, uint32_t* blocks, int* threads,
+                     uint64_t* elements) {
+  double best = 1e300, cells = 0.0, longest = 0.0;
+  int height = 0;
+  for (const int h : {12, 16, 24, 32, 48}) {
+    const double total = batch_cut(m, n, storage, h, out, blocks, threads, &longest);
+    if (total == 0.0) return false;
+    const double t = (storage == 0 ? 0.77 : 0.85) * total / cus + 0.8 * longest;
+    if (t < best) {
+      best = t;
+      height = h;
+    }
+  }
+  batch_cut(m, n, storage, height, out, blocks, threads, &longest);
+  *elements = out[n - 1].offset + NC * out[n - 1].cstride;
+  for (int j = 0; j < n; ++j) cells += m[j].g.ncells;
+  return best < 2e-3 * (storage == 0 ? 0.155 : 0.08) * cells;
+}
+
+hipError_t launch_pair_batch(int storage, bool scaled, void* home, void* second, const Member* members,
+                             const PairMember* pm, const uint16_t* block_member, uint32_t blocks, int threads, bool back,
+                             hipStream_t s) {
+#define CNSF_CASE(ST, SC, T)                                                                                        \
+  if (storage == ST && scaled == SC) {                                                                              \
+    hipLaunchKernelGGL((k_pair_batch<ST, SC>), dim3(blocks), dim3(threads), 0, s, (T*)home, (T*)second, members, pm, \
+                       block_member, back ? 1 : 0);                                                                 \
+    return hipGetLastError();                                                                                       \
+  }
+  CNSF_CASE(0, false, float)
+  CNSF_CASE(1, false, uint16_t)
+  CNSF_CASE(2, false, uint16_t)
+  CNSF_CASE(1, true, uint16_t)
+  CNSF_CASE(2, true, uint16_t)
+#undef CNSF_CASE
+  return hipErrorInvalidValue;
 }
 
 }  // namespace cnsf
