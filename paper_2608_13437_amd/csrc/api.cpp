@@ -227,7 +227,8 @@ struct cnsf_lattice {
   int device = 0;
   int64_t step = 0;
   int parity = 0;
-  Launch lc;
+  Launch lc;                          // as set or, for the lattice's storage type, the default
+  Launch run;                         // as launched
   int* dflag = nullptr;               // device error flag
   DiagPartial* partials = nullptr;    // diagnostics block partials
   DiagPartial* dresult = nullptr;
@@ -264,7 +265,7 @@ void drop_graph(cnsf_lattice* L) {
 
 hipError_t launch_steps(cnsf_lattice* L, int64_t n, hipStream_t s, int& parity) {
   for (int64_t i = 0; i < n; ++i) {
-    hipError_t e = launch_update(L->p.storage, L->pop, L->g, L->ph, L->cd, parity, L->lc, s);
+    hipError_t e = launch_update(L->p.storage, L->pop, L->g, L->ph, L->cd, parity, L->run, s);
     if (e != hipSuccess) return e;
     parity ^= 1;
   }
@@ -404,6 +405,7 @@ int cnsf_create(const cnsf_params* p, void* dev_buf, size_t bytes, void* stream,
   L->stream = (hipStream_t)stream;
   L->bytes = need;
   L->lc = default_launch(p->storage);
+  L->run = lattice_launch(p->storage, L->g.ncells);
   (void)hipGetDevice(&L->device);
   hipError_t e;
   if (dev_buf) {
@@ -464,6 +466,7 @@ int cnsf_set_launch(cnsf_lattice* L, int32_t block, int32_t tile, int32_t grid, 
   L->lc.tile = tile;
   L->lc.grid = grid;
   L->lc.remap = xcd_remap ? 1 : 0;
+  L->run = L->lc;
   L->own_launch = true;
   drop_graph(L);   // the captured updates carry the old shape
   return CNSF_OK;
@@ -690,7 +693,7 @@ int cnsf_step_diagnostics(cnsf_lattice* L, int64_t n, int32_t flags, cnsf_diag* 
       return fail(CNSF_E_NOMEM, "spectral workspace: %s", hipGetErrorString(e));
     }
   }
-  const uint32_t nb = update_blocks(L->g, L->lc);
+  const uint32_t nb = update_blocks(L->g, L->run);
   if (L->step_partials_cap < nb) {
     if (L->step_partials) (void)hipFree(L->step_partials);
     L->step_partials = nullptr;
@@ -712,7 +715,7 @@ int cnsf_step_diagnostics(cnsf_lattice* L, int64_t n, int32_t flags, cnsf_diag* 
   }
   const int64_t step0 = L->step;
   // the first update reduces the sums of the level it reads and writes u, v, w, mu
-  e = launch_update_diag(L->p.storage, L->pop, L->g, L->ph, L->cd, L->parity, L->lc, L->phd, L->step_partials,
+  e = launch_update_diag(L->p.storage, L->pop, L->g, L->ph, L->cd, L->parity, L->run, L->phd, L->step_partials,
                          spectral ? L->fields : nullptr, L->stream);
   if (e != hipSuccess) return hip_fail(e, "fused diagnostic update");
   L->parity ^= 1;
@@ -768,17 +771,17 @@ extern "C" {
 int cnsf_step_diagnostics_static(cnsf_lattice* L, int64_t n, cnsf_diag* d) {
   if (!L || !d) return fail(CNSF_E_INVALID, "NULL argument");
   if (n < 1) return fail(CNSF_E_INVALID, "n = %lld < 1", (long long)n);
-  if (L->lc.grid > STATIC_PARTIALS)
+  if (L->run.grid > STATIC_PARTIALS)
     return fail(CNSF_E_SIZE,
                 "persistent grid of %d blocks: the static workspace holds the partial sums of at most %d blocks",
-                L->lc.grid, STATIC_PARTIALS);
+                L->run.grid, STATIC_PARTIALS);
   (void)hipSetDevice(L->device);
   DiagPartial* sp = nullptr;
   if (int r = static_scratch(L->device, &sp)) return r;
   // the update that reduces the level at entry runs on at most STATIC_PARTIALS
   // blocks (a persistent grid when the lattice has more tiles); the populations
   // it writes do not depend on the launch shape
-  Launch lc = L->lc;
+  Launch lc = L->run;
   uint32_t nb = update_blocks(L->g, lc);
   if (nb > (uint32_t)STATIC_PARTIALS) {
     lc.grid = STATIC_PARTIALS;
