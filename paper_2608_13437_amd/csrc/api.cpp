@@ -231,12 +231,11 @@ struct cnsf_lattice {
   Launch run;                         // as launched
   int* dflag = nullptr;               // device error flag
   DiagPartial* partials = nullptr;    // diagnostics block partials
-  DiagPartial* dresult = nullptr;
+  DiagPartial* result = nullptr;      // two totals, in pinned host memory that the final reduction writes
   double* fields = nullptr;           // spectral workspace (8 doubles per cell)
   double* spec = nullptr;             // shell-spectrum partials and output
   DiagPartial* step_partials = nullptr;  // per-block sums of the fused diagnostic step
   uint32_t step_partials_cap = 0;
-  DiagPartial* dresult2 = nullptr;       // eps sums of the fused diagnostic step
   // small lattices: GRAPH_STEPS updates captured once and replayed (launch-bound otherwise)
   hipStream_t gstream = nullptr;         // capture stream
   hipGraphExec_t gexec = nullptr;
@@ -420,7 +419,7 @@ int cnsf_create(const cnsf_params* p, void* dev_buf, size_t bytes, void* stream,
   }
   e = hipMalloc(&L->dflag, sizeof(int));
   if (e == hipSuccess) e = hipMalloc(&L->partials, sizeof(DiagPartial) * (DIAG_BLOCKS + 1));
-  if (e == hipSuccess) e = hipMalloc(&L->dresult, sizeof(DiagPartial));
+  if (e == hipSuccess) e = hipHostMalloc((void**)&L->result, 2 * sizeof(DiagPartial), hipHostMallocDefault);
   if (e != hipSuccess) {
     cnsf_destroy(L);
     return fail(CNSF_E_NOMEM, "hipMalloc of small buffers: %s", hipGetErrorString(e));
@@ -444,11 +443,10 @@ int cnsf_destroy(cnsf_lattice* L) {
   if (L->owned && L->pop) (void)hipFree(L->pop);
   if (L->dflag) (void)hipFree(L->dflag);
   if (L->partials) (void)hipFree(L->partials);
-  if (L->dresult) (void)hipFree(L->dresult);
+  if (L->result) (void)hipHostFree(L->result);
   if (L->fields) (void)hipFree(L->fields);
   if (L->spec) (void)hipFree(L->spec);
   if (L->step_partials) (void)hipFree(L->step_partials);
-  if (L->dresult2) (void)hipFree(L->dresult2);
   if (L->pair_ws) (void)hipFree(L->pair_ws);
   if (L->tube_ws) (void)hipFree(L->tube_ws);
   drop_graph(L);
@@ -671,12 +669,10 @@ int cnsf_diagnostics(cnsf_lattice* L, int32_t flags, cnsf_diag* d) {
   e = launch_diag_sums(L->p.storage, L->pop, L->g, L->ph, L->phd, L->cd, L->parity, L->partials,
                        spectral ? L->fields : nullptr, L->stream);
   if (e == hipSuccess && spectral) e = launch_spectral(L->g, L->p.dx, L->fields, L->partials, false, L->stream);
-  if (e == hipSuccess) e = launch_diag_final(L->partials, DIAG_BLOCKS, L->dresult, L->stream);
-  DiagPartial r{};
-  if (e == hipSuccess) e = hipMemcpyAsync(&r, L->dresult, sizeof r, hipMemcpyDeviceToHost, L->stream);
+  if (e == hipSuccess) e = launch_diag_final(L->partials, DIAG_BLOCKS, nullptr, 0, nullptr, 0, L->result, L->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
   if (e != hipSuccess) return hip_fail(e, "diagnostics");
-  fill_diag(L, r, spectral, L->step, d);
+  fill_diag(L, L->result[0], spectral, L->step, d);
   return CNSF_OK;
 }
 
@@ -706,13 +702,6 @@ int cnsf_step_diagnostics(cnsf_lattice* L, int64_t n, int32_t flags, cnsf_diag* 
     }
     L->step_partials_cap = nb;
   }
-  if (!L->dresult2) {
-    e = hipMalloc(&L->dresult2, sizeof(DiagPartial));
-    if (e != hipSuccess) {
-      L->dresult2 = nullptr;
-      return fail(CNSF_E_NOMEM, "diagnostic result: %s", hipGetErrorString(e));
-    }
-  }
   const int64_t step0 = L->step;
   // the first update reduces the sums of the level it reads and writes u, v, w, mu
   e = launch_update_diag(L->p.storage, L->pop, L->g, L->ph, L->cd, L->parity, L->run, L->phd, L->step_partials,
@@ -722,17 +711,17 @@ int cnsf_step_diagnostics(cnsf_lattice* L, int64_t n, int32_t flags, cnsf_diag* 
   ++L->step;
   if (spectral) e = launch_spectral(L->g, L->p.dx, L->fields, L->partials, true, L->stream);
   if (e == hipSuccess)
-    e = launch_diag_final2(L->step_partials, (int)nb, L->step_partials + nb, STEP_FINAL_CHUNKS, L->dresult, L->stream);
-  if (e == hipSuccess && spectral) e = launch_diag_final(L->partials, DIAG_BLOCKS, L->dresult2, L->stream);
+    e = launch_diag_final(L->step_partials, (int)nb, L->step_partials + nb, STEP_FINAL_CHUNKS,
+                          spectral ? L->partials : nullptr, DIAG_BLOCKS, L->result, L->stream);
   if (e != hipSuccess) return hip_fail(e, "diagnostic reductions");
   if (int r = cnsf_step(L, n - 1)) return r;
-  DiagPartial r{}, r2{};
-  e = hipMemcpyAsync(&r, L->dresult, sizeof r, hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess && spectral) e = hipMemcpyAsync(&r2, L->dresult2, sizeof r2, hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+  e = hipStreamSynchronize(L->stream);
   if (e != hipSuccess) return hip_fail(e, "step_diagnostics");
-  r.eps_s = r2.eps_s;
-  r.eps_d = r2.eps_d;
+  DiagPartial r = L->result[0];
+  if (spectral) {
+    r.eps_s = L->result[1].eps_s;
+    r.eps_d = L->result[1].eps_d;
+  }
   fill_diag(L, r, spectral, step0, d);
   return CNSF_OK;
 }
@@ -793,7 +782,7 @@ int cnsf_step_diagnostics_static(cnsf_lattice* L, int64_t n, cnsf_diag* d) {
   if (e != hipSuccess) return hip_fail(e, "fused diagnostic update");
   L->parity ^= 1;
   ++L->step;
-  e = launch_diag_final(sp, (int)nb, sp + STATIC_PARTIALS, L->stream);
+  e = launch_diag_final(sp, (int)nb, nullptr, 0, nullptr, 0, sp + STATIC_PARTIALS, L->stream);
   if (e != hipSuccess) return hip_fail(e, "diagnostic reduction");
   if (int r = step_impl(L, n - 1, true, false)) return r;
   DiagPartial r{};

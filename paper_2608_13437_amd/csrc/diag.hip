@@ -907,12 +907,17 @@ __global__ void k_diag_chunks(const DiagPartial* __restrict__ partials, int npar
   if (threadIdx.x == 0) out[blockIdx.x] = tot;
 }
 
-__global__ void k_diag_final(const DiagPartial* __restrict__ partials, int nparts, DiagPartial* __restrict__ out) {
+// Totals of one or two sets of partials, one block per set.  A block's latency is all this costs (4 to 7 us),
+// so the two sets of a diagnostic step share a launch.
+__global__ void k_diag_final(const DiagPartial* __restrict__ first, int nfirst, const DiagPartial* __restrict__ second,
+                             int nsecond, DiagPartial* __restrict__ out) {
+  const DiagPartial* partials = blockIdx.x ? second : first;
+  const int nparts = blockIdx.x ? nsecond : nfirst;
   DiagPartial acc;
   part_zero(acc);
   for (int i = threadIdx.x; i < nparts; i += DB) part_add(acc, partials[i]);
   DiagPartial tot = block_reduce(acc);
-  if (threadIdx.x == 0) *out = tot;
+  if (threadIdx.x == 0) out[blockIdx.x] = tot;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1106,20 +1111,19 @@ hipError_t launch_spectrum(const Geom& g, double* fields, double* partial, doubl
   return hipGetLastError();
 }
 
-hipError_t launch_diag_final(DiagPartial* partials, int nparts, DiagPartial* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(DB), 0, s, partials, nparts, out);
+hipError_t launch_diag_final(const DiagPartial* partials, int nparts, DiagPartial* tmp, int ntmp,
+                             const DiagPartial* second, int nsecond, DiagPartial* out, hipStream_t s) {
+  if (tmp && ntmp > 0 && nparts > 4 * DB) {
+    const int nb = std::min(ntmp, (nparts + 4 * DB - 1) / (4 * DB));
+    const int chunk = (nparts + nb - 1) / nb;
+    hipLaunchKernelGGL(k_diag_chunks, dim3(nb), dim3(DB), 0, s, partials, nparts, chunk, tmp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    partials = tmp;
+    nparts = nb;
+  }
+  hipLaunchKernelGGL(k_diag_final, dim3(second ? 2 : 1), dim3(DB), 0, s, partials, nparts, second, nsecond, out);
   return hipGetLastError();
-}
-
-hipError_t launch_diag_final2(DiagPartial* partials, int nparts, DiagPartial* tmp, int ntmp, DiagPartial* out,
-                              hipStream_t s) {
-  if (!tmp || ntmp < 1 || nparts <= 4 * DB) return launch_diag_final(partials, nparts, out, s);
-  const int nb = std::min(ntmp, (nparts + 4 * DB - 1) / (4 * DB));
-  const int chunk = (nparts + nb - 1) / nb;
-  hipLaunchKernelGGL(k_diag_chunks, dim3(nb), dim3(DB), 0, s, partials, nparts, chunk, tmp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_diag_final(tmp, nb, out, s);
 }
 
 }  // namespace cnsf

@@ -101,11 +101,11 @@ hipError_t launch_velocity(int storage, const void* pop, const Geom& g, const Co
 // their eps fields, or (full) whole partials with the other fields neutral.
 hipError_t launch_spectral(const Geom& g, double dx, double* fields, DiagPartial* partials, bool full,
                            hipStream_t s);
-hipError_t launch_diag_final(DiagPartial* partials, int nparts, DiagPartial* out, hipStream_t s);
-// The same total in two levels when there are many partials: chunks reduced
-// into tmp (at most ntmp of them) by many blocks, then tmp by one block.
-hipError_t launch_diag_final2(DiagPartial* partials, int nparts, DiagPartial* tmp, int ntmp, DiagPartial* out,
-                              hipStream_t s);
+// Total of the partials into out[0], in two levels when there are many (chunks reduced into tmp, at most ntmp
+// of them, by many blocks; tmp may be NULL), and of a second set, unless that is NULL, into out[1].  out may be
+// host memory that the device can write.
+hipError_t launch_diag_final(const DiagPartial* partials, int nparts, DiagPartial* tmp, int ntmp,
+                             const DiagPartial* second, int nsecond, DiagPartial* out, hipStream_t s);
 // Shell spectrum of the velocity held in fields (u, v, w: the first 3 * ncells
 // doubles, written by launch_diag_sums); uses fields[4 ncells, 7 ncells) as
 // workspace and partial (SHELL_PARTS * nz * spectrum_shells(nx) doubles).  Writes nout
