@@ -327,7 +327,8 @@ int cnsf_batch_get_moments(cnsf_batch* b, int32_t j, double* out, int32_t where)
 int cnsf_batch_set_launch(cnsf_batch* b, int32_t block, int32_t tile, int32_t grid, int32_t graph_steps);
 /* The batch's current launch shape (any output pointer may be NULL). */
 int cnsf_batch_get_launch(const cnsf_batch* b, int32_t* block, int32_t* tile, int32_t* grid, int32_t* graph_steps);
-/* Time candidate launch shapes with HIP events and keep the fastest; results
+/* Time candidate launch shapes with HIP events and keep the fastest, and single steps if
+ * mode 1's paired ones (which need their second array for this) are not faster; results
  * are cached in the JSON file `cache_path` (may be NULL) keyed by the batch's
  * shape signature. */
 int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per_trial);

@@ -246,6 +246,22 @@ static bool batch_pair_ready(cnsf_batch* b) {
   return b->pair_ws != nullptr;
 }
 
+// Single steps from now on.
+static void batch_refuse_pairs(cnsf_batch* b) {
+  if (b->pair_ws) (void)hipStreamSynchronize(b->stream);
+  batch_drop_pairs(b);
+  b->pair_decided = true;
+}
+
+// n steps (a multiple of four) from an even level, forward and back.
+static hipError_t batch_pair_steps(cnsf_batch* b, int64_t n) {
+  hipError_t e = hipSuccess;
+  for (int64_t i = 0; i < n / 2 && e == hipSuccess; ++i)
+    e = launch_pair_batch(b->storage, b->scaled, b->base, b->pair_ws, b->dm, b->dpair, b->dpair_block, b->pair_blocks,
+                          b->pair_threads, (i & 1) != 0, b->stream);
+  return e;
+}
+
 static hipError_t batch_launch_steps(cnsf_batch* b, int64_t n, hipStream_t s, int& parity) {
   for (int64_t i = 0; i < n; ++i) {
     hipError_t e = launch_batch(b->storage, b->scaled, b->base, b->dm, b->dtile, b->total_tiles, b->tile,
@@ -442,11 +458,10 @@ int cnsf_batch_step(cnsf_batch* b, int64_t n, int32_t mode) {
     // paired passes, forward and back, of four updates
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (b->stream) (void)hipStreamIsCapturing(b->stream, &cap);
-    if (e == hipSuccess && left >= 4 && cap == hipStreamCaptureStatusNone && batch_pair_ready(b))
-      for (; e == hipSuccess && left >= 4; left -= 4)
-        for (int back = 0; back < 2 && e == hipSuccess; ++back)
-          e = launch_pair_batch(b->storage, b->scaled, b->base, b->pair_ws, b->dm, b->dpair, b->dpair_block, b->pair_blocks,
-                                b->pair_threads, back != 0, b->stream);
+    if (e == hipSuccess && left >= 4 && cap == hipStreamCaptureStatusNone && batch_pair_ready(b)) {
+      e = batch_pair_steps(b, left / 4 * 4);
+      left %= 4;
+    }
     const int64_t reps = left / b->graph_steps;
     if (e == hipSuccess && reps > 0) {
       if (!b->gexec) {
@@ -514,7 +529,8 @@ static std::string batch_signature(const cnsf_batch* b) {
   return os.str();
 }
 
-static bool cache_lookup(const char* path, const std::string& key, int& block, int& tile, int& grid) {
+// `pairs`: 0 if single steps were measured faster than paired ones, 1 if not, -1 if the entry does not say.
+static bool cache_lookup(const char* path, const std::string& key, int& block, int& tile, int& grid, int& pairs) {
   if (!path) return false;
   std::ifstream in(path);
   if (!in) return false;
@@ -523,11 +539,12 @@ static bool cache_lookup(const char* path, const std::string& key, int& block, i
   const std::string s = ss.str();
   const size_t pos = s.find("\"" + key + "\"");
   if (pos == std::string::npos) return false;
-  return sscanf(s.c_str() + pos + key.size() + 2, " : {\"block\": %d, \"tile\": %d, \"grid\": %d}", &block, &tile,
-                &grid) == 3;
+  pairs = -1;
+  return sscanf(s.c_str() + pos + key.size() + 2, " : {\"block\": %d, \"tile\": %d, \"grid\": %d, \"pairs\": %d}", &block,
+                &tile, &grid, &pairs) >= 3;
 }
 
-static void cache_store(const char* path, const std::string& key, int block, int tile, int grid) {
+static void cache_store(const char* path, const std::string& key, int block, int tile, int grid, int pairs) {
   if (!path) return;
   std::string body;
   {
@@ -539,7 +556,8 @@ static void cache_store(const char* path, const std::string& key, int block, int
     }
   }
   char entry[256];
-  snprintf(entry, sizeof entry, "\"%s\": {\"block\": %d, \"tile\": %d, \"grid\": %d}", key.c_str(), block, tile, grid);
+  snprintf(entry, sizeof entry, "\"%s\": {\"block\": %d, \"tile\": %d, \"grid\": %d, \"pairs\": %d}", key.c_str(), block,
+           tile, grid, pairs);
   const size_t close = body.rfind('}');
   if (body.empty() || close == std::string::npos) {
     body = std::string("{\n  ") + entry + "\n}\n";
@@ -559,8 +577,11 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
   steps_per_trial += steps_per_trial % 2;
   (void)hipSetDevice(b->device);
   const std::string key = batch_signature(b);
-  int bb, tt, gg;
-  if (cache_lookup(cache_path, key, bb, tt, gg)) return cnsf_batch_set_launch(b, bb, tt, gg, b->graph_steps);
+  int bb, tt, gg, pp;
+  if (cache_lookup(cache_path, key, bb, tt, gg, pp)) {
+    if (pp == 0) batch_refuse_pairs(b);
+    return cnsf_batch_set_launch(b, bb, tt, gg, b->graph_steps);
+  }
   // trial steps change the state: keep a copy and restore it afterwards
   void* save = nullptr;
   hipError_t e = hipMalloc(&save, b->bytes);
@@ -595,6 +616,21 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
       bestc = c;
     }
   }
+  // paired steps against the best shape of single ones (16-bit batches in a fast array: FP16 64 members
+  // of 32^3 to 96^3 1.55 ms per step single and 1.59 paired, 1.87 and 1.64 in a plain array)
+  int pairs = -1;
+  if (e == hipSuccess && batch_pair_ready(b)) {
+    const int64_t n = (steps_per_trial + 3) / 4 * 4;
+    e = batch_pair_steps(b, 4);
+    if (e == hipSuccess) e = hipEventRecord(t0, b->stream);
+    if (e == hipSuccess) e = batch_pair_steps(b, n);
+    if (e == hipSuccess) e = hipEventRecord(t1, b->stream);
+    if (e == hipSuccess) e = hipEventSynchronize(t1);
+    float ms = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, t0, t1);
+    pairs = ms / (float)n < best / (float)steps_per_trial;
+    if (e == hipSuccess && !pairs) batch_refuse_pairs(b);
+  }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
   if (e == hipSuccess) e = hipMemcpyAsync(b->base, save, b->bytes, hipMemcpyDeviceToDevice, b->stream);
@@ -603,7 +639,7 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
   b->parity = parity0;
   if (e != hipSuccess) return hip_fail(e, "autotune");
   if (int r = cnsf_batch_set_launch(b, bestc.block, bestc.tile, bestc.grid, b->graph_steps)) return r;
-  cache_store(cache_path, key, bestc.block, bestc.tile, bestc.grid);
+  cache_store(cache_path, key, bestc.block, bestc.tile, bestc.grid, pairs);
   return CNSF_OK;
 }
 

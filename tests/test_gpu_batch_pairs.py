@@ -49,3 +49,43 @@ def test_paired_batch_equals_single_updates(storage, scale, spacing):
     assert torch.equal(a.buf, b.buf)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("pairs", [None, 0, 1])
+def test_autotune_keeps_the_state_and_honours_its_cache(tmp_path, pairs):
+    """A cached entry says whether paired steps were the faster ones; without a cache the
+    trials restore the state, at an odd level too."""
+    import json
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2608_13437_amd as cnsf
+    prms = [W.random_params(64, 64, 64, seed=j) for j in range(32)]
+    Q = W.smooth_random_case(64, 64, 64).Q0
+    a, b = cnsf.Batch(prms), cnsf.Batch(prms)
+    for B in (a, b):
+        for j in range(len(prms)):
+            B.set_state(j, Q)
+        B.step(3, B.MODE_LAUNCH)
+    cache = tmp_path / "tuned.json"
+    if pairs is not None:
+        first = cnsf.Batch(prms)
+        first.autotune(str(cache), steps_per_trial=4)
+        first.close()
+        entries = json.loads(cache.read_text())
+        for v in entries.values():
+            v["pairs"] = pairs
+        cache.write_text(json.dumps(entries))
+    torch.cuda.synchronize()
+    b.autotune(str(cache) if pairs is not None else None, steps_per_trial=4)
+    assert torch.equal(a.buf, b.buf)
+    free0 = torch.cuda.mem_get_info()[0]
+    a.step(9, a.MODE_LAUNCH)
+    b.step(9, b.MODE_GRAPH)
+    torch.cuda.synchronize()
+    taken = free0 - torch.cuda.mem_get_info()[0]
+    if pairs is not None:
+        assert (taken >= b.nbytes // 2) == bool(pairs)
+    assert torch.equal(a.buf, b.buf)
+    a.close()
+    b.close()
