@@ -59,8 +59,9 @@ def stats(path, out, command, bench_log=None):
         for line in open(bench_log):
             if line.startswith("{") and '"metric"' in line:
                 rec = json.loads(line)
-                lines.append(f"# bench.py in the same process: ms_per_step {rec['ms_per_step']} "
-                             f"(mean of the even and odd launches), {rec['value']} {rec['unit']}")
+                lines.append(f"# bench.py in the same process: {rec['roofline']['ms_per_update']} ms per single update "
+                             f"(mean of the even and odd launches); one call of {rec['steps']} steps "
+                             f"{rec['ms_per_step']} ms per step, {rec['value']} {rec['unit']}")
                 trace = os.path.join(os.path.dirname(path), "run_kernel_trace.csv")
                 if os.path.exists(trace):
                     # the table below also counts the placement probe's launches on
