@@ -282,6 +282,7 @@ bool pair_ready(cnsf_lattice* L, bool may_alloc) {
   if (L->own_launch) return false;
   if (L->pair_decided || !may_alloc) return L->pair_ws != nullptr;
   L->pair_decided = true;
+  const RelaxedCapture relaxed;
   size_t freeb = 0, total = 0;
   int cus = 0;
   if (hipMemGetInfo(&freeb, &total) != hipSuccess ||
@@ -303,6 +304,7 @@ bool tube_ready(cnsf_lattice* L, bool may_alloc) {
   if (L->own_launch) return false;
   if (!L->tube_decided && may_alloc) {
     L->tube_decided = true;
+    const RelaxedCapture relaxed;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) cus = 0;
     if (cus > 0 && tube_plan(L->g, L->p.storage, cus, &L->tube) && L->tube.xw != (int)L->g.nx &&

@@ -19,4 +19,14 @@ Phys to_float(const PhysD& d);
 Geom derive_geom(const cnsf_params* p, const PhysD& ph);
 Codec derive_codec(const cnsf_params* p, const PhysD& ph);
 
+// While one lives, allocations of this thread leave alone a capture that runs on some other stream:
+// a workspace made by a step call must not end the caller's capture.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+
 }  // namespace cnsf

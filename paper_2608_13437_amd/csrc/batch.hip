@@ -19,6 +19,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <new>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -211,9 +212,10 @@ static void batch_drop_pairs(cnsf_batch* b) {
 }
 
 // Whether the batch advances by paired passes; the first call decides and allocates.
-static bool batch_pair_ready(cnsf_batch* b) {
+static bool batch_pair_ready(cnsf_batch* b) try {
   if (b->pair_decided) return b->pair_ws != nullptr;
   b->pair_decided = true;
+  const RelaxedCapture relaxed;
   const size_t eb = elem_bytes(b->storage), n = b->m.size();
   size_t freeb = 0, total = 0;
   int cus = 0;
@@ -237,12 +239,16 @@ static bool batch_pair_ready(cnsf_batch* b) {
   hipError_t e = hipMalloc(&b->pair_ws, elements * eb);
   if (e == hipSuccess) e = hipMalloc(&b->dpair, sizeof(PairMember) * n);
   if (e == hipSuccess) e = hipMalloc(&b->dpair_block, sizeof(uint16_t) * owner.size());
-  if (e == hipSuccess) e = hipMemcpy(b->dpair, pm.data(), sizeof(PairMember) * n, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(b->dpair_block, owner.data(), sizeof(uint16_t) * owner.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpyAsync(b->dpair, pm.data(), sizeof(PairMember) * n, hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(b->dpair_block, owner.data(), sizeof(uint16_t) * owner.size(), hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();   // single updates then
     batch_drop_pairs(b);
   }
+  return b->pair_ws != nullptr;
+} catch (const std::bad_alloc&) {   // host memory for the tables: single steps then
   return b->pair_ws != nullptr;
 }
 

@@ -104,3 +104,41 @@ def test_paired_passes_give_their_workspace_back():
         torch.cuda.synchronize()
         free.append(torch.cuda.mem_get_info()[0])
     assert abs(free[2] - free[1]) < 64 << 20
+
+
+@pytest.mark.parametrize("kind", ["pairs", "windows", "batch"])
+def test_first_steps_beside_a_capture_on_another_stream(kind):
+    """The workspaces of multi-step calls are allocated by the first call; a capture that
+    runs on another stream meanwhile must survive that, and the steps come out the same."""
+    import torch
+    cnsf = _cnsf()
+    print(f"case {kind}", flush=True)
+    c = W.sod(256, 4, 4) if kind == "windows" else W.smooth_random_case(64, 64, 64)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        if kind == "batch":
+            a, b = cnsf.Batch([c.params] * 32), cnsf.Batch([c.params] * 32)
+            for B in (a, b):
+                for j in range(32):
+                    B.set_state(j, c.Q0)
+        else:
+            a, b = cnsf.Lattice(c.params), cnsf.Lattice(c.params)
+            a.set_state(c.Q0)
+            b.set_state(c.Q0)
+    x = torch.zeros(64, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        x += 1.0
+        b.step(8, b.MODE_GRAPH) if kind == "batch" else b.step(8)
+        x += 1.0
+    for _ in range(8):
+        a.step(1, a.MODE_LAUNCH) if kind == "batch" else a.step(1)
+    for _ in range(2):
+        g.replay()
+    torch.cuda.synchronize()
+    assert float(x[0]) == 4.0
+    assert torch.equal(a.buf, b.buf)
+    del g
+    a.close()
+    b.close()
