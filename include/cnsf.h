@@ -182,10 +182,11 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * lattice's stream is itself being captured, the updates are plain launches.
  * Periodic lattices for which it is faster (most of 96^3 and more) advance four
  * updates at a time, two per pass over memory, with the same results bit for
- * bit, when n >= 4 (5 from an odd level).  The first such call allocates a
- * workspace, kept until cnsf_destroy: the array's size up to 2 GiB, an eighth
- * of the array beyond, at most an eighth of the free device memory; without it
- * (or after cnsf_set_launch) the lattice stays on single updates.  Thin lattices
+ * bit, when n >= 4 (5 from an odd level).  The call with which this would have
+ * saved the cost of it (the first one, but for short calls of small lattices)
+ * allocates a workspace, kept until cnsf_destroy: the array's size up to 2 GiB (16-bit
+ * storage: 8 GiB), beyond that 2 GiB or an eighth of the array, never more than
+ * an eighth of the free device memory; without it (or after cnsf_set_launch) the lattice stays on single updates.  Thin lattices
  * (ny * nz of a few tens of cells at most: tubes, channels, columns) likewise
  * make several updates per launch, with a workspace of the array's size unless
  * they have no more than 256 cells.

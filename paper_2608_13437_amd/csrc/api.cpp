@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -242,7 +243,8 @@ struct cnsf_lattice {
   // two updates per pass: workspace and cut of the lattice, decided at the first call that can use them
   void* pair_ws = nullptr;
   PairPlan pair;
-  bool pair_decided = false;
+  bool pair_decided = false, pair_wanted = false;
+  double pair_missed = 0.0;              // us that pairs would have saved so far
   // several updates per launch: second array (unless one window holds the lattice) and windows
   void* tube_ws = nullptr;
   TubePlan tube;
@@ -251,6 +253,57 @@ struct cnsf_lattice {
 };
 
 namespace {
+// Pinned host memory for the totals that a readout's final reduction writes: 64 places of two to a page.
+// Allocating such memory takes 150 us, more than a small lattice's readout, so lattices share pages; one page is
+// kept when its last place is given back, the others are freed.
+class TotalsPool {
+ public:
+  hipError_t take(DiagPartial** out) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (Page& p : pages_)
+      if (~p.used) {
+        const int i = __builtin_ctzll(~p.used);
+        p.used |= 1ull << i;
+        *out = p.base + 2 * i;
+        return hipSuccess;
+      }
+    const RelaxedCapture relaxed;
+    DiagPartial* base = nullptr;
+    const hipError_t e = hipHostMalloc((void**)&base, 128 * sizeof(DiagPartial), hipHostMallocPortable);
+    if (e != hipSuccess) return e;
+    try {
+      pages_.push_back(Page{base, 1ull});
+    } catch (const std::bad_alloc&) {
+      (void)hipHostFree(base);
+      return hipErrorOutOfMemory;
+    }
+    *out = base;
+    return hipSuccess;
+  }
+  void give_back(DiagPartial* place) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (size_t j = 0; j < pages_.size(); ++j) {
+      Page& p = pages_[j];
+      if (place < p.base || place >= p.base + 128) continue;
+      p.used &= ~(1ull << ((place - p.base) / 2));
+      if (!p.used && pages_.size() > 1) {
+        (void)hipHostFree(p.base);
+        pages_.erase(pages_.begin() + (std::ptrdiff_t)j);
+      }
+      return;
+    }
+  }
+
+ private:
+  struct Page {
+    DiagPartial* base;
+    uint64_t used;   // bit i: place i is taken
+  };
+  std::mutex mu_;
+  std::vector<Page> pages_;
+};
+TotalsPool& g_totals = *new TotalsPool;   // lives until the process ends: handles may be destroyed at exit
+
 // Lattices up to this many cells step through a replayed HIP graph when a call
 // asks for at least 2 GRAPH_STEPS updates: their update takes a few
 // microseconds, about what one launch costs.  Larger lattices launch directly.
@@ -273,28 +326,44 @@ hipError_t launch_steps(cnsf_lattice* L, int64_t n, hipStream_t s, int& parity) 
 
 // Updates of one pass forward and one back (pair.hip).
 constexpr int64_t PAIR_STEPS = 4;
-// Workspace of the paired passes: a second array for lattices up to 2 GiB, else an eighth of the
-// array (512^3 FP32: 3.5 GB of 52.6), and never more than an eighth of the free device memory.
-constexpr size_t PAIR_WS_WHOLE = (size_t)2 << 30;
+// Workspace of the paired passes: a second array for FP32 lattices up to 2 GiB and 16-bit ones up to 8, else 2 GiB or
+// an eighth of the array (512^3 FP32: 3.5 GB of 52.6 used), and never more than an eighth of the free device memory.
+// Slabs start a block for fewer planes: FP16 (us per update, slabs / second array) 256^3 952 / 925, 288^3 1963
+// (single updates) / 1727, 320^3 2125 / 1980, BF16 320^3 2210 / 2010.  FP32 between 2 and 13 GB goes either way
+// (224^3 1060 / 1180, 256^3 1530 / 1400, 288^3 2560 / 2550 to 2990, 320^3 2980 / 3000): slabs, the smaller.
+constexpr size_t pair_ws_whole(int storage) { return (size_t)(storage == CNSF_STORAGE_FP32 ? 2 : 8) << 30; }
+constexpr size_t PAIR_WS_SLABS = (size_t)2 << 30;
+// What making a workspace costs (us; 64^3 FP32, five steps: first call 208 without, 320 with; 4.5 GB 1.5 ms).
+constexpr double pair_ws_cost(size_t bytes) { return 100.0 + 3e-7 * (double)bytes; }
 
-// Whether `L` advances by paired passes; the first call decides and allocates (if it may).
-bool pair_ready(cnsf_lattice* L, bool may_alloc) {
+// Whether `L` makes n updates by paired passes.  The first call decides; the workspace is made (if it may be) by
+// the call with which pairs would have saved its cost, so that a short run does not pay for what it cannot use.
+bool pair_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   if (L->own_launch) return false;
-  if (L->pair_decided || !may_alloc) return L->pair_ws != nullptr;
-  L->pair_decided = true;
+  if (L->pair_ws) return true;
+  if (!may_alloc || (L->pair_decided && !L->pair_wanted)) return false;
   const RelaxedCapture relaxed;
-  size_t freeb = 0, total = 0;
-  int cus = 0;
-  if (hipMemGetInfo(&freeb, &total) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
+  if (!L->pair_decided) {
+    L->pair_decided = true;
+    size_t freeb = 0, total = 0;
+    int cus = 0;
+    if (hipMemGetInfo(&freeb, &total) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    const size_t whole = L->bytes <= pair_ws_whole(L->p.storage) ? L->bytes : 0;
+    const size_t budget = std::min(std::max({whole, PAIR_WS_SLABS, L->bytes / 8}), freeb / 8);
+    L->pair_wanted = pair_plan(L->g, L->p.storage, budget, cus, &L->pair);
+    if (!L->pair_wanted) return false;
   }
-  const size_t budget = std::min(std::max(PAIR_WS_WHOLE, L->bytes / 8), freeb / 8);
-  if (!pair_plan(L->g, L->p.storage, budget, cus, &L->pair)) return false;
-  if (hipMalloc(&L->pair_ws, pair_workspace_bytes(L->g, L->p.storage, L->pair.split)) != hipSuccess) {
+  L->pair_missed += (double)n * L->pair.gain;
+  const size_t bytes = pair_workspace_bytes(L->g, L->p.storage, L->pair.split);
+  if (L->pair_missed < pair_ws_cost(bytes)) return false;
+  if (hipMalloc(&L->pair_ws, bytes) != hipSuccess) {
     (void)hipGetLastError();   // single updates then
     L->pair_ws = nullptr;
+    L->pair_wanted = false;
   }
   return L->pair_ws != nullptr;
 }
@@ -421,7 +490,6 @@ int cnsf_create(const cnsf_params* p, void* dev_buf, size_t bytes, void* stream,
   }
   e = hipMalloc(&L->dflag, sizeof(int));
   if (e == hipSuccess) e = hipMalloc(&L->partials, sizeof(DiagPartial) * (DIAG_BLOCKS + 1));
-  if (e == hipSuccess) e = hipHostMalloc((void**)&L->result, 2 * sizeof(DiagPartial), hipHostMallocDefault);
   if (e != hipSuccess) {
     cnsf_destroy(L);
     return fail(CNSF_E_NOMEM, "hipMalloc of small buffers: %s", hipGetErrorString(e));
@@ -445,7 +513,7 @@ int cnsf_destroy(cnsf_lattice* L) {
   if (L->owned && L->pop) (void)hipFree(L->pop);
   if (L->dflag) (void)hipFree(L->dflag);
   if (L->partials) (void)hipFree(L->partials);
-  if (L->result) (void)hipHostFree(L->result);
+  if (L->result) g_totals.give_back(L->result);
   if (L->fields) (void)hipFree(L->fields);
   if (L->spec) (void)hipFree(L->spec);
   if (L->step_partials) (void)hipFree(L->step_partials);
@@ -530,7 +598,7 @@ static int step_impl(cnsf_lattice* L, int64_t n, bool may_multi, bool may_alloc)
       --left;
     }
     if (e == hipSuccess) e = tube_steps(L, left, &left);
-  } else if (!plain && may_multi && n - L->parity >= PAIR_STEPS && pair_ready(L, may_alloc)) {
+  } else if (!plain && may_multi && n - L->parity >= PAIR_STEPS && pair_ready(L, n, may_alloc)) {
     if (L->parity) {
       e = launch_steps(L, 1, L->stream, L->parity);
       --left;
@@ -656,9 +724,18 @@ static void fill_diag(const cnsf_lattice* L, const DiagPartial& r, bool spectral
   d->nonfinite = (int64_t)r.nonfinite;
 }
 
+// The pinned totals of the readouts.
+static int result_ready(cnsf_lattice* L) {
+  if (L->result) return CNSF_OK;
+  const hipError_t e = g_totals.take(&L->result);
+  if (e != hipSuccess) return fail(CNSF_E_NOMEM, "diagnostic result: %s", hipGetErrorString(e));
+  return CNSF_OK;
+}
+
 int cnsf_diagnostics(cnsf_lattice* L, int32_t flags, cnsf_diag* d) {
   if (!L || !d) return fail(CNSF_E_INVALID, "NULL argument");
   (void)hipSetDevice(L->device);
+  if (int r = result_ready(L)) return r;
   const bool spectral = (flags & CNSF_DIAG_SPECTRAL) && L->g.bc_x == CNSF_BC_PERIODIC;
   hipError_t e = hipSuccess;
   if (spectral && !L->fields) {
@@ -682,6 +759,7 @@ int cnsf_step_diagnostics(cnsf_lattice* L, int64_t n, int32_t flags, cnsf_diag* 
   if (!L || !d) return fail(CNSF_E_INVALID, "NULL argument");
   if (n < 1) return fail(CNSF_E_INVALID, "n = %lld < 1", (long long)n);
   (void)hipSetDevice(L->device);
+  if (int r = result_ready(L)) return r;
   const bool spectral = (flags & CNSF_DIAG_SPECTRAL) && L->g.bc_x == CNSF_BC_PERIODIC;
   hipError_t e = hipSuccess;
   if (spectral && !L->fields) {

@@ -35,6 +35,7 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // columns of a tile along x and y.
 struct PairPlan {
   int split = 0, slab = 0, chunk = 0, tx = 0, ty = 0;
+  double gain = 0.0;   // us per update over single updates, by the plan's times
 };
 // The plan of a lattice with at most `budget` workspace bytes on `cus` compute units; false if
 // single updates are at least as fast or the lattice is not served.

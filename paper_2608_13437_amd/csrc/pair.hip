@@ -466,7 +466,7 @@ bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out
         const double t = (double)nslab * rounds * (h + 3) * plane;
         if (t < best) {
           best = t;
-          *out = PairPlan{split, slab, h, tx, ty};
+          *out = PairPlan{split, slab, h, tx, ty, 0.0};
         }
       }
     };
@@ -477,6 +477,7 @@ bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out
     }
   }
   const double cell = storage == 0 ? (cached ? 0.12 : 0.155) : (cached ? 0.072 : 0.077);
+  out->gain = 1e-3 * cell * g.ncells - 0.5 * best;
   return 1.05 * best < 2e-3 * cell * g.ncells;
 }
 

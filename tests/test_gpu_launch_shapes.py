@@ -48,3 +48,46 @@ def test_own_shape_equals_default_shape(nx, ny, nz, storage, bc):
             assert np.allclose(da[k], db[k], rtol=0.0, atol=1e-12 * size), (k, da[k], db[k])
     a.close()
     b.close()
+
+
+def test_readouts_of_many_lattices_share_pinned_pages():
+    """More lattices alive than one page of totals has places, destroyed and made again in
+    another order, read out from several threads: each gets its own sums."""
+    import threading
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2608_13437_amd as cnsf
+    c = W.smooth_random_case(9, 5, 4)
+    made = {}
+
+    def make(j):
+        made[j] = cnsf.Lattice(c.params)
+        made[j].set_state(c.Q0 * np.where(np.arange(14) < 5, 1.0 + j, 0.0)[:, None, None, None])
+
+    def read(js):
+        for j in js:
+            for _ in range(3):
+                got.setdefault(j, []).append(made[j].diagnostics(spectral=False)["mass"])
+
+    for j in range(150):
+        make(j)
+    got = {}
+    read(range(150))
+    for j in list(range(0, 150, 2)) + [149, 1]:
+        made.pop(j).close()
+    for j in range(0, 60, 2):
+        make(j)
+    got.clear()
+    parts = [list(made)[k::4] for k in range(4)]
+    threads = [threading.Thread(target=read, args=(p,)) for p in parts]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    mass = float(c.Q0[0].sum())
+    assert len(got) == len(made)
+    for j, m in got.items():
+        assert np.allclose(m, (1.0 + j) * mass, rtol=1e-5, atol=0.0), j
+    for L in made.values():
+        L.close()

@@ -46,16 +46,17 @@ def _state(prm, seed):
 
 # nx, ny, nz, storage, storage scale, steps per call
 CASES = [
-    (64, 64, 64, W.STORAGE_FP32, 0.0, (1, 5, 4, 7)),      # one tile along x, second array
-    (80, 79, 80, W.STORAGE_FP32, 0.0, (4, 2)),            # whole rows of three, one row in the last tile
+    (64, 64, 64, W.STORAGE_FP32, 0.0, (1, 5, 4, 7, 40, 9)),   # one tile along x, second array
+    (80, 79, 80, W.STORAGE_FP32, 0.0, (4, 2, 18)),            # whole rows of three, one row in the last tile
     (96, 95, 100, W.STORAGE_FP32, 0.0, (4, 6)),           # the longest whole rows
-    (150, 147, 150, W.STORAGE_FP32, 0.0, (5, 4)),         # tiles of 64, 64 and 22 columns, ragged rows
+    (150, 147, 150, W.STORAGE_FP32, 0.0, (5, 4, 14)),     # tiles of 64, 64 and 22 columns, ragged rows
     (128, 128, 127, W.STORAGE_FP16, 0.0, (4, 3, 9)),      # 16-bit links
     (128, 128, 128, W.STORAGE_BF16, 0.0, (8,)),
-    (128, 126, 128, W.STORAGE_FP16, 0.5, (5, 4)),         # scaled codes, two rows in the last tile
+    (128, 126, 128, W.STORAGE_FP16, 0.5, (5, 4, 9)),         # scaled codes, two rows in the last tile
     (192, 192, 192, W.STORAGE_FP32, 0.0, (4, 1, 10)),     # slabs through a workspace
     (256, 254, 192, W.STORAGE_FP32, 0.0, (4, 5)),         # slabs of whole slot groups, two rows in the last tile
-    (320, 256, 256, W.STORAGE_FP16, 0.0, (4, 6)),         # 16-bit slabs
+    (320, 256, 256, W.STORAGE_FP16, 0.0, (4, 6)),         # 16-bit, second array
+    (384, 340, 340, W.STORAGE_FP16, 0.0, (4, 6, 8)),         # 16-bit slabs (from 8 GiB on)
     (448, 440, 424, W.STORAGE_FP32, 0.0, (4,)),           # non-temporal stores (from 32 GB on)
 ]
 
@@ -130,9 +131,9 @@ def test_first_steps_beside_a_capture_on_another_stream(kind):
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         x += 1.0
-        b.step(8, b.MODE_GRAPH) if kind == "batch" else b.step(8)
+        b.step(66, b.MODE_GRAPH) if kind == "batch" else b.step(66)
         x += 1.0
-    for _ in range(8):
+    for _ in range(66):
         a.step(1, a.MODE_LAUNCH) if kind == "batch" else a.step(1)
     for _ in range(2):
         g.replay()
