@@ -342,30 +342,35 @@ bool pair_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   if (L->own_launch) return false;
   if (L->pair_ws) return true;
   if (!may_alloc || (L->pair_decided && !L->pair_wanted)) return false;
-  const RelaxedCapture relaxed;
+  const size_t whole = L->bytes <= pair_ws_whole(L->p.storage) ? L->bytes : 0;
+  const size_t budget = std::max({whole, PAIR_WS_SLABS, L->bytes / 8});
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
   if (!L->pair_decided) {
     L->pair_decided = true;
-    size_t freeb = 0, total = 0;
-    int cus = 0;
-    if (hipMemGetInfo(&freeb, &total) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-    const size_t whole = L->bytes <= pair_ws_whole(L->p.storage) ? L->bytes : 0;
-    const size_t budget = std::min(std::max({whole, PAIR_WS_SLABS, L->bytes / 8}), freeb / 8);
     L->pair_wanted = pair_plan(L->g, L->p.storage, budget, cus, &L->pair);
     if (!L->pair_wanted) return false;
   }
   L->pair_missed += (double)n * L->pair.gain;
-  const size_t bytes = pair_workspace_bytes(L->g, L->p.storage, L->pair.split);
+  size_t bytes = pair_workspace_bytes(L->g, L->p.storage, L->pair.split);
   if (L->pair_missed < pair_ws_cost(bytes)) return false;
-  if (hipMalloc(&L->pair_ws, bytes) != hipSuccess) {
-    (void)hipGetLastError();   // single updates then
+  // what the free memory leaves of the plan (asking takes 30 us: not before it matters)
+  const RelaxedCapture relaxed;
+  size_t freeb = 0, total = 0;
+  L->pair_wanted = hipMemGetInfo(&freeb, &total) == hipSuccess;
+  if (L->pair_wanted && bytes > freeb / 8) {
+    L->pair_wanted = pair_plan(L->g, L->p.storage, std::min(budget, freeb / 8), cus, &L->pair);
+    bytes = pair_workspace_bytes(L->g, L->p.storage, L->pair.split);
+  }
+  if (L->pair_wanted && hipMalloc(&L->pair_ws, bytes) != hipSuccess) {
     L->pair_ws = nullptr;
     L->pair_wanted = false;
   }
-  return L->pair_ws != nullptr;
+  if (!L->pair_wanted) (void)hipGetLastError();   // single updates then
+  return L->pair_wanted;
 }
 
 // Whether `L` advances by windows of several updates (tube.hip); decides and allocates like pair_ready.
