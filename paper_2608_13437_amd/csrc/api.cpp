@@ -269,7 +269,8 @@ class TotalsPool {
       }
     const RelaxedCapture relaxed;
     DiagPartial* base = nullptr;
-    const hipError_t e = hipHostMalloc((void**)&base, 128 * sizeof(DiagPartial), hipHostMallocPortable);
+    const hipError_t e = hipHostMalloc((void**)&base, 128 * sizeof(DiagPartial),
+                                       hipHostMallocPortable | hipHostMallocCoherent);
     if (e != hipSuccess) return e;
     try {
       pages_.push_back(Page{base, 1ull});

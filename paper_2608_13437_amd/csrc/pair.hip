@@ -439,10 +439,10 @@ static double plane_us(int storage, int nx, double columns, bool cached) {
 // 128-byte lines (9.6-11.2), shorter as fewer of the tile's columns exist, about 2.5 more with
 // rows of partial lines, 6.6-8.2 when the lattice fits the 256 MB last-level cache; 16-bit 7.3
 // (7.0-7.4) and one or two more with rows of partial lines.  Single updates (ns per cell): FP32
-// 0.155 (0.12 in cache), 16-bit 0.077 (0.072).  Pairs must win by 5%.  Taken (us per update, single
+// 0.155 (0.12 in cache), 16-bit 0.077 (0.063).  Pairs must win by 5%.  Taken (us per update, single
 // / pairs): FP32 64^3 31 / 23, 80^3 62 / 49, 96^3 132 / 79, 100^3 173 / 133, 128^3 336 / 188, 150^3
 // 578 / 470; 16-bit 128^3 163 / 123, 192^3 552 / 450, 240^3 1118 / 972.  Left: FP32 48^3 and 16-bit
-// 64^3 (equal), 16-bit 96^3 60 / 73, 200^3 647 / 713, 272^3 1624 / 1759.
+// 64^3 (equal), 16-bit 96^3 55 / 73, 200^3 647 / 713, 272^3 1624 / 1759.
 bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out) {
   if (g.bc_x != 0) return false;
   const size_t e = storage == 0 ? 4 : 2;
@@ -476,7 +476,7 @@ bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out
       if (split + 2 <= nz) consider(split, slab);
     }
   }
-  const double cell = storage == 0 ? (cached ? 0.12 : 0.155) : (cached ? 0.072 : 0.077);
+  const double cell = storage == 0 ? (cached ? 0.12 : 0.155) : (cached ? 0.063 : 0.077);
   out->gain = 1e-3 * cell * g.ncells - 0.5 * best;
   return 1.05 * best < 2e-3 * cell * g.ncells;
 }

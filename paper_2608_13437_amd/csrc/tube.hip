@@ -15,9 +15,9 @@
 //
 // Measured on MI355X (us per update, single updates in a replayed graph -> windows): FP32 16 x 4 x 4
 // (one window) 4.9 -> 2.2, Sod 256 x 4 x 4 5.0 -> 3.6, Becker 1024 x 4 x 4 6.3 -> 4.3, 1024 x 1 x 1 4.7 ->
-// 2.3; FP16 Sod 256 7.8 -> 4.0.  What bounds it: an update is 2.2 us of one wave per SIMD (700 vector
+// 2.3; FP16 Sod 256 7.8 -> 4.0.  What bounds it: an update is 2.2 to 2.65 us of one wave per SIMD (750 vector
 // instructions at 4 cycles, 168 LDS accesses, two barriers), a launch with its loads and stores
-// about 9.5 us.
+// 5.3 us and more (Sod: 15.9 us with four updates, 21.2 with six).
 #include <algorithm>
 
 #include "cnsf_impl.h"
@@ -156,10 +156,12 @@ k_tube(const typename Store<ST>::T* src, typename Store<ST>::T* dst, const Geom 
   }
 }
 
-// Windows of a lattice: planes a window holds, and the even number of updates per launch that is
-// fastest by the times above (16-bit 2.85 us an update), if that beats single updates by 5%: those
-// take 4.7 us and 0.085 ns per cell (16-bit 7.6 and 0.05).  Cross-sections of 32 cells and more
-// stay with single updates: windows of 8 planes make two updates a launch (128 x 8 x 4 7.6 us against 5.1).
+// Windows of a lattice: planes a window holds, and the even number of updates per launch that is fastest, if
+// that beats single updates.  A launch of s updates takes (us, within 10% over cross-sections of 1 to 32 cells,
+// 64 to 3000 planes) 8.0 + 2.03 s + 0.27 per MB read and written, 16-bit 8.0 + 2.45 s + 0.45; single updates take
+// 4.0 + 0.095 per thousand cells, 16-bit 4.6 + 0.043.  Measured (us per update, windows / single): FP32 4 x 4
+// cross-sections of 64, 256, 1024 and 3000 planes 3.2 / 4.0, 3.7 / 4.3, 4.4 / 5.4 and, left, 10.9 / 8.7; left too
+// FP32 5 x 4 4.8 / 4.3 and 4 x 6 5.2 / 4.4 of 256 planes, FP16 4 x 6 of 256 and 1024 5.3 / 4.7 and 9.6 / 5.5.
 bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
   const uint32_t cross = g.ny * g.nz;
   if (cross > TUBE_THREADS / 4u) return false;
@@ -168,16 +170,19 @@ bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
     *out = TubePlan{nx, 1 << 20};
     return true;
   }
+  const bool fp32 = storage == 0;
+  const double cell_mb = NP * (fp32 ? 4e-6 : 2e-6);
   double best = 1e300;
   for (int s = 2; 2 * s < most && s <= 64; s += 2) {
     const int keep = most - 2 * s, blocks = (nx + keep - 1) / keep, rounds = (blocks + cus - 1) / cus;
-    const double t = rounds * (9.5 + (storage == 0 ? 2.2 : 2.85) * s) / s;
+    const double mb = cell_mb * ((double)blocks * TUBE_THREADS + g.ncells);
+    const double t = (rounds * (8.0 + (fp32 ? 2.03 : 2.45) * s) + (fp32 ? 0.27 : 0.45) * mb) / s;
     if (t < best) {
       best = t;
       *out = TubePlan{most, s};
     }
   }
-  return 1.05 * best < (storage == 0 ? 4.7 + 8.5e-5 * g.ncells : 7.6 + 5e-5 * g.ncells);
+  return best < (fp32 ? 4.0 + 9.5e-5 * g.ncells : 4.6 + 4.3e-5 * g.ncells);
 }
 
 template <int ST, int BC, bool SC>
