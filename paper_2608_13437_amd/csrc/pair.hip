@@ -442,7 +442,7 @@ static double plane_us(int storage, int nx, double columns, bool cached) {
 // 0.155 (0.12 in cache), 16-bit 0.077 (0.063).  Pairs must win by 5%.  Taken (us per update, single
 // / pairs): FP32 64^3 31 / 23, 80^3 62 / 49, 96^3 132 / 79, 100^3 173 / 133, 128^3 336 / 188, 150^3
 // 578 / 470; 16-bit 128^3 163 / 123, 192^3 552 / 450, 240^3 1118 / 972.  Left: FP32 48^3 and 16-bit
-// 64^3 (equal), 16-bit 96^3 55 / 73, 200^3 647 / 713, 272^3 1624 / 1759.
+// 64^3 (equal), 16-bit 96^3 55 / 73, 200^3 647 / 713.
 bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out) {
   if (g.bc_x != 0) return false;
   const size_t e = storage == 0 ? 4 : 2;
