@@ -190,7 +190,10 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * (ny * nz of a few tens of cells at most: tubes, channels, columns) likewise
  * make several updates per launch, with a workspace of the array's size unless
  * they have no more than 256 cells.
- * CNSF_E_DEVICE if a launch fails. */
+ * CNSF_E_DEVICE if a launch is refused; cnsf_get_info then reports the level that
+ * the array holds.  Where large lattices are shifted within their array by slabs, a
+ * pass refused half way leaves no level there: every call that needs one
+ * returns CNSF_E_DEVICE until cnsf_set_state (from plane 0) or cnsf_import_populations. */
 int cnsf_step(cnsf_lattice* lat, int64_t n);
 
 /* Time the update on this lattice's population array: one untimed update, then

@@ -250,6 +250,7 @@ struct cnsf_lattice {
   TubePlan tube;
   bool tube_decided = false;
   bool own_launch = false;               // the caller chose the launch shape of the update
+  bool torn = false;                     // a pass was refused half way: the array holds no time level
 };
 
 namespace {
@@ -325,6 +326,22 @@ hipError_t launch_steps(cnsf_lattice* L, int64_t n, hipStream_t s, int& parity) 
   return hipSuccess;
 }
 
+// n updates of the lattice on its stream; step and parity follow what was launched.
+hipError_t single_steps(cnsf_lattice* L, int64_t n) {
+  hipError_t e = hipSuccess;
+  for (int64_t i = 0; i < n && e == hipSuccess; ++i) {
+    e = launch_steps(L, 1, L->stream, L->parity);
+    if (e == hipSuccess) ++L->step;
+  }
+  return e;
+}
+
+// CNSF_OK if the array holds a time level.
+int level_ready(const cnsf_lattice* L) {
+  if (!L->torn) return CNSF_OK;
+  return fail(CNSF_E_DEVICE, "an update was refused half way through the array: set a state or import populations");
+}
+
 // Updates of one pass forward and one back (pair.hip).
 constexpr int64_t PAIR_STEPS = 4;
 // Workspace of the paired passes: a second array for FP32 lattices up to 2 GiB and 16-bit ones up to 8, else 2 GiB or
@@ -391,14 +408,18 @@ bool tube_ready(cnsf_lattice* L, bool may_alloc) {
   return L->tube.xw == (int)L->g.nx || L->tube_ws != nullptr;
 }
 
-// Up to n updates from an even level by windows (an even number); *left: n less what was enqueued.
+// Up to n updates from an even level by windows (an even number); *left: n less what was enqueued.  Windows
+// that go to the second array count with those that come back.
 hipError_t tube_steps(cnsf_lattice* L, int64_t n, int64_t* left) {
   constexpr int64_t WHOLE_STEPS = 4096;   // updates of one launch of a lattice that fits one window
   hipError_t e = hipSuccess;
   if (L->tube.xw == (int)L->g.nx) {
     *left = n & 1;
-    for (n -= *left; n > 0 && e == hipSuccess; n -= std::min(n, WHOLE_STEPS))
-      e = launch_tube(L->p.storage, L->pop, L->pop, L->g, L->ph, L->cd, L->tube.xw, (int)std::min(n, WHOLE_STEPS), L->stream);
+    for (n -= *left; n > 0 && e == hipSuccess; n -= std::min(n, WHOLE_STEPS)) {
+      const int u = (int)std::min(n, WHOLE_STEPS);
+      e = launch_tube(L->p.storage, L->pop, L->pop, L->g, L->ph, L->cd, L->tube.xw, u, L->stream);
+      if (e == hipSuccess) L->step += u;
+    }
     return e;
   }
   // an even number of launches of even numbers of updates, as equal as they can be
@@ -408,11 +429,17 @@ hipError_t tube_steps(cnsf_lattice* L, int64_t n, int64_t* left) {
   launches += launches & 1;
   if (launches > units) units = launches = units & ~(int64_t)1;   // two updates a launch, an odd number of launches
   *left = n - 2 * units;
+  int64_t home = 0;   // units whose windows came back
   for (int64_t j = 0; j < launches && e == hipSuccess; ++j) {
     const int64_t u = units * (j + 1) / launches - units * j / launches;
     void* a = j & 1 ? L->tube_ws : L->pop;
     void* b = j & 1 ? L->pop : L->tube_ws;
     e = launch_tube(L->p.storage, a, b, L->g, L->ph, L->cd, L->tube.xw, (int)(2 * u), L->stream);
+    if (e == hipSuccess && (j & 1)) {
+      const int64_t now = units * (j + 1) / launches;
+      L->step += 2 * (now - home);
+      home = now;
+    }
   }
   return e;
 }
@@ -583,6 +610,7 @@ static int set_state_impl(cnsf_lattice* L, const double* Q, int32_t z0, int32_t 
   if (z0 == 0) {
     L->step = 0;
     L->parity = 0;
+    L->torn = false;
   }
   if (bad) return fail(CNSF_E_STATE, "state has rho <= 0, p <= 0 or a non-finite value in z-planes [%d, %d)", z0, z0 + nzs);
   return CNSF_OK;
@@ -591,6 +619,7 @@ static int set_state_impl(cnsf_lattice* L, const double* Q, int32_t z0, int32_t 
 // n >= 0 updates; may_multi: several per pass where that is faster, may_alloc: the workspace of
 // those may be allocated now.
 static int step_impl(cnsf_lattice* L, int64_t n, bool may_multi, bool may_alloc) {
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   int64_t left = n;
   hipError_t e = hipSuccess;
@@ -598,32 +627,33 @@ static int step_impl(cnsf_lattice* L, int64_t n, bool may_multi, bool may_alloc)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (L->stream) (void)hipStreamIsCapturing(L->stream, &cap);
   const bool plain = cap != hipStreamCaptureStatusNone;
-  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, may_alloc)) {
+  auto even = [&] {   // to an even level
     if (L->parity) {
-      e = launch_steps(L, 1, L->stream, L->parity);
+      e = single_steps(L, 1);
       --left;
     }
+  };
+  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, may_alloc)) {
+    even();
     if (e == hipSuccess) e = tube_steps(L, left, &left);
   } else if (!plain && may_multi && n - L->parity >= PAIR_STEPS && pair_ready(L, n, may_alloc)) {
-    if (L->parity) {
-      e = launch_steps(L, 1, L->stream, L->parity);
-      --left;
-    }
-    for (; e == hipSuccess && left >= PAIR_STEPS; left -= PAIR_STEPS)
+    even();
+    for (; e == hipSuccess && left >= PAIR_STEPS; left -= PAIR_STEPS) {
       for (int back = 0; back < 2 && e == hipSuccess; ++back)
-        e = launch_pair(L->p.storage, L->pop, L->pair_ws, L->g, L->ph, L->cd, L->pair, back != 0, L->stream);
-  } else if (!plain && L->g.ncells <= GRAPH_MAX_CELLS && n >= 2 * GRAPH_STEPS) {
-    if (L->parity) {
-      e = launch_steps(L, 1, L->stream, L->parity);
-      --left;
+        e = launch_pair(L->p.storage, L->pop, L->pair_ws, L->g, L->ph, L->cd, L->pair, back != 0, L->stream, &L->torn);
+      if (e == hipSuccess) L->step += PAIR_STEPS;
     }
+  } else if (!plain && L->g.ncells <= GRAPH_MAX_CELLS && n >= 2 * GRAPH_STEPS) {
+    even();
     if (e == hipSuccess && !L->gexec) e = build_graph(L);
     // the replays run on the caller's stream, in its order with its other work
-    for (; e == hipSuccess && left >= GRAPH_STEPS; left -= GRAPH_STEPS) e = hipGraphLaunch(L->gexec, L->stream);
+    for (; e == hipSuccess && left >= GRAPH_STEPS; left -= GRAPH_STEPS) {
+      e = hipGraphLaunch(L->gexec, L->stream);
+      if (e == hipSuccess) L->step += GRAPH_STEPS;
+    }
   }
-  if (e == hipSuccess) e = launch_steps(L, left, L->stream, L->parity);
+  if (e == hipSuccess) e = single_steps(L, left);
   if (e != hipSuccess) return hip_fail(e, "update launch");
-  L->step += n;
   return CNSF_OK;
 }
 
@@ -668,6 +698,7 @@ int cnsf_get_primitives(cnsf_lattice* L, double* out, int32_t z0, int32_t nzs, i
   if (!L || !out) return fail(CNSF_E_INVALID, "NULL argument");
   if (z0 < 0 || nzs < 0 || z0 + nzs > (int)L->g.nz) return fail(CNSF_E_SIZE, "slab [%d, %d) outside nz = %u", z0, z0 + nzs, L->g.nz);
   if (where != CNSF_HOST && where != CNSF_DEVICE) return fail(CNSF_E_INVALID, "where = %d", where);
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   const uint32_t nslab = (uint32_t)nzs * L->g.nxy;
   const uint32_t cell0 = (uint32_t)z0 * L->g.nxy;
@@ -692,6 +723,7 @@ int cnsf_get_moments(cnsf_lattice* L, double* out, int32_t z0, int32_t nzs, int3
   if (!L || !out) return fail(CNSF_E_INVALID, "NULL argument");
   if (z0 < 0 || nzs < 0 || z0 + nzs > (int)L->g.nz) return fail(CNSF_E_SIZE, "slab [%d, %d) outside nz = %u", z0, z0 + nzs, L->g.nz);
   if (where != CNSF_HOST && where != CNSF_DEVICE) return fail(CNSF_E_INVALID, "where = %d", where);
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   const uint32_t nslab = (uint32_t)nzs * L->g.nxy;
   const uint32_t cell0 = (uint32_t)z0 * L->g.nxy;
@@ -740,6 +772,7 @@ static int result_ready(cnsf_lattice* L) {
 
 int cnsf_diagnostics(cnsf_lattice* L, int32_t flags, cnsf_diag* d) {
   if (!L || !d) return fail(CNSF_E_INVALID, "NULL argument");
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   if (int r = result_ready(L)) return r;
   const bool spectral = (flags & CNSF_DIAG_SPECTRAL) && L->g.bc_x == CNSF_BC_PERIODIC;
@@ -764,6 +797,7 @@ int cnsf_diagnostics(cnsf_lattice* L, int32_t flags, cnsf_diag* d) {
 int cnsf_step_diagnostics(cnsf_lattice* L, int64_t n, int32_t flags, cnsf_diag* d) {
   if (!L || !d) return fail(CNSF_E_INVALID, "NULL argument");
   if (n < 1) return fail(CNSF_E_INVALID, "n = %lld < 1", (long long)n);
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   if (int r = result_ready(L)) return r;
   const bool spectral = (flags & CNSF_DIAG_SPECTRAL) && L->g.bc_x == CNSF_BC_PERIODIC;
@@ -850,6 +884,7 @@ int cnsf_step_diagnostics_static(cnsf_lattice* L, int64_t n, cnsf_diag* d) {
     return fail(CNSF_E_SIZE,
                 "persistent grid of %d blocks: the static workspace holds the partial sums of at most %d blocks",
                 L->run.grid, STATIC_PARTIALS);
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   DiagPartial* sp = nullptr;
   if (int r = static_scratch(L->device, &sp)) return r;
@@ -893,6 +928,7 @@ int cnsf_spectrum(cnsf_lattice* L, double* E, int32_t nshells, int32_t where) {
   if (int r = cnsf_spectrum_shells(L, &need)) return r;
   if (nshells < need) return fail(CNSF_E_SIZE, "spectrum needs %d shells, got %d", need, nshells);
   if (where != CNSF_HOST && where != CNSF_DEVICE) return fail(CNSF_E_INVALID, "where must be HOST or DEVICE");
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   hipError_t e = hipSuccess;
   if (!L->fields) {
@@ -943,6 +979,7 @@ int cnsf_get_info(const cnsf_lattice* L, int64_t* step, int32_t* parity, size_t*
 int cnsf_export_populations(cnsf_lattice* L, void* host, size_t bytes, int64_t* step, int32_t* parity) {
   if (!L || !host) return fail(CNSF_E_INVALID, "NULL argument");
   if (bytes != L->bytes) return fail(CNSF_E_SIZE, "checkpoint buffer %zu != %zu bytes", bytes, L->bytes);
+  if (int r = level_ready(L)) return r;
   (void)hipSetDevice(L->device);
   hipError_t e = hipMemcpyAsync(host, L->pop, bytes, hipMemcpyDeviceToHost, L->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
@@ -962,6 +999,7 @@ int cnsf_import_populations(cnsf_lattice* L, const void* host, size_t bytes, int
   if (e != hipSuccess) return hip_fail(e, "import");
   L->step = step;
   L->parity = parity;
+  L->torn = false;
   return CNSF_OK;
 }
 

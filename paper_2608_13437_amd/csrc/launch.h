@@ -41,9 +41,11 @@ struct PairPlan {
 // single updates are at least as fast or the lattice is not served.
 bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out);
 size_t pair_workspace_bytes(const Geom& g, int storage, int split);
-// One pass of a lattice at an even level: forward from the array to the shifted place, or back.
+// One pass of a lattice at an even level: forward from the array to the shifted place, or back.  If a launch is
+// refused the array holds the level from which the last forward pass began, unless *torn is set: slabs had begun
+// to overwrite it.
 hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd,
-                       const PairPlan& pl, bool back, hipStream_t s);
+                       const PairPlan& pl, bool back, hipStream_t s, bool* torn);
 
 // One member of a batch in the device table, and its cut for paired passes (second array: member
 // after member, each laid out like a lattice of its own).

@@ -483,7 +483,7 @@ bool pair_plan(const Geom& g, int storage, size_t budget, int cus, PairPlan* out
 
 template <int ST, bool SC>
 static hipError_t launch_pair_t(void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd, const PairPlan& pl,
-                                bool back, hipStream_t s) {
+                                bool back, hipStream_t s, bool* torn) {
   using T = typename Store<ST>::T;
   const bool whole = pl.split >= (int)g.nz;
   const uint64_t cs_scr = (uint64_t)NV * groups((uint64_t)pl.split * g.nxy);
@@ -504,11 +504,21 @@ static hipError_t launch_pair_t(void* pop, void* ws, const Geom& g, const Phys& 
     return (uint32_t)(z < p.split ? z : z - p.split) * g.nxy;
   };
   const dim3 pg((g.nxy + 255) / 256, NC);
+  // slabs: the array is no longer the level of the forward pass's start once its second slab has run (the first
+  // one writes the workspace only)
+  bool moving = !whole && back;
+  hipError_t e = hipSuccess;
+  auto refused = [&] {
+    e = hipGetLastError();
+    if (e != hipSuccess) *torn = moving;
+    return e != hipSuccess;
+  };
   if (!whole) {
     T* b;
     uint64_t cs;
     const uint32_t c0 = cell(src, back ? nz - 1 : 0, b, cs);
     hipLaunchKernelGGL(k_plane_save<T>, pg, dim3(256), 0, s, (const T*)b, cs, c0, g.nxy, wrap, (uint64_t)NV * groups(g.nxy));
+    if (refused()) return e;
   }
   const int ntx = ((int)g.nx + pl.tx - 1) / pl.tx, ncol = ntx * (((int)g.ny + pl.ty - 1) / pl.ty);
   const int threads = PNI + (ring_columns(pl.tx, pl.ty, (int)g.nx) + 63) / 64 * 64;
@@ -522,22 +532,27 @@ static hipError_t launch_pair_t(void* pop, void* ws, const Geom& g, const Phys& 
     const int nch = (z1 - z0 + pl.chunk - 1) / pl.chunk;
     hipLaunchKernelGGL(kernel, dim3(ncol * nch), dim3(threads), 0, s, src, dst, g, ph, cd, z0, z1, pl.chunk, pl.tx,
                        pl.ty, ntx, ncol, (const T*)wrap, wrap_z, over, over_z);
+    if (refused()) return e;
+    moving = !whole && (back || j > 0);
   }
   if (!whole) {
     T* b;
     uint64_t cs;
     const uint32_t c0 = cell(dst, back ? 0 : nz - 1, b, cs);
     hipLaunchKernelGGL(k_plane_put<T>, pg, dim3(256), 0, s, (const T*)over, groups(g.nxy), g.nxy, back ? 5 : 6, b, cs, c0);
+    if (refused()) return e;
   }
-  return hipGetLastError();
+  return e;
 }
 
 hipError_t launch_pair(int storage, void* pop, void* ws, const Geom& g, const Phys& ph, const Codec& cd,
-                       const PairPlan& pl, bool back, hipStream_t s) {
+                       const PairPlan& pl, bool back, hipStream_t s, bool* torn) {
   const bool sc = cd.scaled != 0;
-  if (storage == 0) return launch_pair_t<0, false>(pop, ws, g, ph, cd, pl, back, s);
-  if (storage == 1) return (sc ? launch_pair_t<1, true> : launch_pair_t<1, false>)(pop, ws, g, ph, cd, pl, back, s);
-  return (sc ? launch_pair_t<2, true> : launch_pair_t<2, false>)(pop, ws, g, ph, cd, pl, back, s);
+  *torn = false;
+  if (storage == 0) return launch_pair_t<0, false>(pop, ws, g, ph, cd, pl, back, s, torn);
+  if (storage == 1)
+    return (sc ? launch_pair_t<1, true> : launch_pair_t<1, false>)(pop, ws, g, ph, cd, pl, back, s, torn);
+  return (sc ? launch_pair_t<2, true> : launch_pair_t<2, false>)(pop, ws, g, ph, cd, pl, back, s, torn);
 }
 
 // Tiles of every member for blocks of about `height` planes; the blocks' total time and that of the

@@ -1,0 +1,159 @@
+"""What the library's calls launch and allocate, seen without a GPU.
+
+A child process loads tests/hip_double.cpp in place of the HIP runtime: kernels
+are written down instead of run, addresses are not backed by memory, and a test
+can refuse a launch or limit the free memory.  Only the host code is under test
+here; results are compared on the GPU.
+"""
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = '''
+import ctypes as C, json, sys
+hip = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+sys.modules["torch"] = None            # its own HIP runtime stays out of this process
+sys.path.insert(0, {root!r})
+import paper_2608_13437_amd as cnsf
+import workloads as W
+hip.double_launches.restype = hip.double_held.restype = C.c_size_t
+hip.double_name.restype = C.c_char_p
+hip.double_name.argtypes = hip.double_block.argtypes = [C.c_size_t]
+hip.double_refuse.argtypes = [C.c_long]
+hip.double_memory.argtypes = [C.c_size_t]
+hip.double_cost.argtypes = [C.c_char_p, C.c_double]
+
+def lattice(prm):
+    return cnsf.cnsf_create(cnsf.make_params(prm), 0, 0, 0)
+
+def box(nx, ny, nz, storage=0, **kw):
+    return dict(W.random_params(nx, ny, nz), storage=storage, **kw)
+
+def batch(prms):
+    h = C.c_void_p()
+    ps = (cnsf.cnsf_params * len(prms))(*[cnsf.make_params(p) for p in prms])
+    cnsf._check(cnsf.library().cnsf_batch_create(ps, len(prms), None, 0, None, C.byref(h)))
+    return h
+
+def status(f, *a):
+    """0, or the status a call fails with."""
+    try:
+        f(*a)
+        return 0
+    except cnsf.CnsfError as e:
+        return e.status
+
+def launched():
+    """Names of the kernels launched since the last call of this, in order."""
+    out = [hip.double_name(i).decode() for i in range(hip.double_launches())]
+    hip.double_forget()
+    return out
+'''
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    """host(code): runs code after PRELUDE in a child process, returns what it passes to done()."""
+    import paper_2608_13437_amd as m
+    if not os.path.exists(m.LIB_PATH):
+        from paper_2608_13437_amd import build
+        build.build()
+    so = tmp_path_factory.mktemp("double") / "hip_double.so"
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include",
+                    os.path.join(ROOT, "tests", "hip_double.cpp"), "-o", str(so)], check=True)
+
+    def run(code):
+        src = PRELUDE.format(root=ROOT) + "done = lambda x: print('\\n' + json.dumps(x))\n" + textwrap.dedent(code)
+        r = subprocess.run([sys.executable, "-c", src, str(so)], capture_output=True, text=True, timeout=120, cwd=ROOT)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.strip().splitlines()[-1])
+
+    return run
+
+
+def test_refused_launch_leaves_the_level_that_ran(host):
+    """A launch refused within a multi-step call: step and parity are those of the level in the
+    array (which the passes and windows that had not come home have not touched)."""
+    r = host('''
+        out = {}
+        # name: lattice, launches before the refused one, updates in the array then
+        cases = dict(
+            pair_forward=(box(128, 128, 128), 4, 8), pair_back=(box(128, 128, 128), 5, 8),
+            odd_entry=(box(128, 128, 128), 0, 0),
+            slabs_first=(box(192, 192, 192), 0, 0), slab_zero=(box(192, 192, 192), 1, 0),
+            slab_one=(box(192, 192, 192), 2, 0),
+            window_out=(box(256, 4, 4), 4, None), window_home=(box(256, 4, 4), 5, None),
+            single=(box(24, 24, 24, bc_x=W.BC_NOSLIP, wall_u=[[0, 0, 0]] * 2, wall_T=[0, 0]), 7, 7))
+        for name, (prm, before, at) in cases.items():
+            L = lattice(prm)
+            cnsf.cnsf_step(L, 200)         # the workspace is there
+            if name == "odd_entry":
+                cnsf.cnsf_step(L, 1)
+            s0 = cnsf.cnsf_get_info(L)[0]
+            launched()
+            hip.double_refuse(before)
+            n = 40 if name != "single" else 20
+            st = status(cnsf.cnsf_step, L, n)
+            step, parity, _ = cnsf.cnsf_get_info(L)
+            hip.double_refuse(-1)
+            ran = launched()
+            out[name] = [st, step - s0, parity, (step & 1), at, ran,
+                         status(cnsf.cnsf_diagnostics, L, 0), status(cnsf.cnsf_step, L, 8)]
+        done(out)
+    ''')
+    for name, (st, ran, parity, odd, at, kernels, diag, again) in r.items():
+        assert st == 3, name                                   # CNSF_E_DEVICE
+        assert parity == odd, name
+        assert diag == 0 and again == 0, name                  # the array holds a level
+        if at is not None:
+            assert ran == at, (name, ran, kernels)
+    assert set(r["pair_back"][5]) == {"k_pair"} and set(r["window_home"][5]) == {"k_tube"}
+    # windows: only those that came home count, alike for both
+    assert 0 < r["window_home"][1] < 40 and r["window_home"][1] == r["window_out"][1]
+
+
+def test_refused_launch_within_slabs_is_not_passed_over(host):
+    """Slabs shift the lattice within its own array: a pass refused half way leaves no level there,
+    and every call that needs one says so until a state is set or imported."""
+    r = host('''
+        out = {}
+        for name in ("third_slab", "put", "back", "within_back"):
+            L = lattice(box(512, 512, 512))
+            cnsf.cnsf_step(L, 4)
+            launched()
+            cnsf.cnsf_step(L, 4)
+            one = launched()                  # save, slabs, put; the same backwards
+            half = len(one) // 2
+            before = {"third_slab": 3, "put": half - 1, "back": half, "within_back": half + 2}[name]
+            hip.double_refuse(before)
+            st = [status(cnsf.cnsf_step, L, 4)]
+            hip.double_refuse(-1)
+            buf = (C.c_double * 8)()
+            nb = cnsf.cnsf_get_info(L)[2]
+            step = cnsf.cnsf_get_info(L)[0]
+            d = cnsf.cnsf_diag()
+            lib = cnsf.library()
+            launched()
+            st += [lib.cnsf_step(L, 1), lib.cnsf_diagnostics(L, 0, C.byref(d)),
+                   lib.cnsf_step_diagnostics(L, 3, 0, C.byref(d)), lib.cnsf_step_diagnostics_static(L, 3, C.byref(d)),
+                   lib.cnsf_get_moments(L, buf, 0, 1, 1), lib.cnsf_get_primitives(L, buf, 0, 1, 1),
+                   lib.cnsf_spectrum(L, buf, 1000, 1), lib.cnsf_export_populations(L, buf, nb, None, None),
+                   lib.cnsf_probe_update_ms(L, 1, buf)]
+            ran = launched()
+            mended = [lib.cnsf_import_populations(L, buf, nb, 0, 0) if name == "put" else
+                      lib.cnsf_set_state(L, buf, 0, 512, 1), lib.cnsf_step(L, 8), lib.cnsf_diagnostics(L, 0, C.byref(d))]
+            out[name] = [one, st, ran, step, mended, cnsf.cnsf_get_info(L)[0]]
+        done(out)
+    ''')
+    for name, (one, st, ran, step, mended, after) in r.items():
+        assert one[0] == "k_plane_save" and one[-1] == "k_plane_put" and one.count("k_pair") >= 6, (name, one)
+        assert st == [3] * len(st), (name, st)
+        assert ran == [], name
+        assert step == 8 and mended == [0, 0, 0] and after == 8, name
