@@ -391,8 +391,8 @@ bool pair_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   return L->pair_wanted;
 }
 
-// Whether `L` advances by windows of several updates (tube.hip); decides and allocates like pair_ready.
-bool tube_ready(cnsf_lattice* L, bool may_alloc) {
+// Whether `L` makes n updates by windows of several (tube.hip); decides and allocates like pair_ready.
+bool tube_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   if (L->own_launch) return false;
   if (!L->tube_decided && may_alloc) {
     L->tube_decided = true;
@@ -405,7 +405,7 @@ bool tube_ready(cnsf_lattice* L, bool may_alloc) {
       L->tube_ws = nullptr;
     }
   }
-  return L->tube.xw == (int)L->g.nx || L->tube_ws != nullptr;
+  return n >= L->tube.least && (L->tube.xw == (int)L->g.nx || L->tube_ws != nullptr);
 }
 
 // Up to n updates from an even level by windows (an even number); *left: n less what was enqueued.  Windows
@@ -633,7 +633,7 @@ static int step_impl(cnsf_lattice* L, int64_t n, bool may_multi, bool may_alloc)
       --left;
     }
   };
-  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, may_alloc)) {
+  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, n - L->parity, may_alloc)) {
     even();
     if (e == hipSuccess) e = tube_steps(L, left, &left);
   } else if (!plain && may_multi && n - L->parity >= PAIR_STEPS && pair_ready(L, n, may_alloc)) {

@@ -69,9 +69,10 @@ hipError_t launch_pair_batch(int storage, bool scaled, void* home, void* second,
                              hipStream_t s);
 
 // Several updates per launch for thin lattices (tube.hip): planes of a window and the even number
-// of updates per launch.  A window as long as the lattice takes any number, in place.
+// of updates per launch; calls of fewer than `least` updates are faster as single ones.  A window as
+// long as the lattice takes any number, in place.
 struct TubePlan {
-  int xw = 0, steps = 0;
+  int xw = 0, steps = 0, least = 4;
 };
 bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out);
 // `steps` (even) updates of a lattice at an even level, from src to dst (both laid out as the array).

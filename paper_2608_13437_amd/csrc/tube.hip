@@ -167,10 +167,14 @@ bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
   if (cross > TUBE_THREADS / 4u) return false;
   const int most = TUBE_THREADS / (int)cross, nx = (int)g.nx;
   if (nx <= most) {
-    *out = TubePlan{nx, 1 << 20};
+    *out = TubePlan{nx, 1 << 20, 4};
     return true;
   }
   const bool fp32 = storage == 0;
+  // Short calls: windows go out and come back, two launches.  Measured (us per call, windows / single; the worst of
+  // FP32 and 16-bit, walls and periodic): 4 updates of 1024 x 1 x 1 18.8 / 20.2 and 3000 x 2 x 2 22.8 / 22.0, but
+  // 1024 x 4 x 2 23.5 / 19.9; 6 of 1024 x 3 x 3 31.1 / 32.6 but of 1024 x 3 x 4 34.4 / 31.5; 8 of 1024 x 4 x 4 41.9 / 43.8.
+  const int least = most >= 64 ? 4 : most >= 28 ? 6 : 8;
   const double cell_mb = NP * (fp32 ? 4e-6 : 2e-6);
   double best = 1e300;
   for (int s = 2; 2 * s < most && s <= 64; s += 2) {
@@ -179,7 +183,7 @@ bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
     const double t = (rounds * (8.0 + (fp32 ? 2.03 : 2.45) * s) + (fp32 ? 0.27 : 0.45) * mb) / s;
     if (t < best) {
       best = t;
-      *out = TubePlan{most, s};
+      *out = TubePlan{most, s, least};
     }
   }
   return best < (fp32 ? 4.0 + 9.5e-5 * g.ncells : 4.6 + 4.3e-5 * g.ncells);

@@ -157,3 +157,38 @@ def test_refused_launch_within_slabs_is_not_passed_over(host):
         assert st == [3] * len(st), (name, st)
         assert ran == [], name
         assert step == 8 and mended == [0, 0, 0] and after == 8, name
+
+
+def test_short_calls_of_windowed_lattices(host):
+    """Windows go out to the second array and come back, two launches: calls too short for that
+    to pay are single updates (from the even level on), longer ones windows."""
+    r = host('''
+        out = {}
+        for dims in ((1024, 4, 4), (256, 3, 4), (256, 3, 3), (1024, 4, 2), (300, 2, 2), (1024, 1, 1), (16, 4, 4)):
+            for storage in (0, 1):
+                L = lattice(box(*dims, storage=storage))
+                cnsf.cnsf_step(L, 400)
+                launched()
+                seen = []
+                for n in range(4, 11):
+                    for odd in (0, 1):
+                        if odd:
+                            cnsf.cnsf_step(L, 1)
+                            launched()
+                        cnsf.cnsf_step(L, n + odd)
+                        seen.append([n, odd, launched()])
+                        if cnsf.cnsf_get_info(L)[1]:
+                            cnsf.cnsf_step(L, 1)
+                            launched()
+                out["%d %d %d %d" % (*dims, storage)] = seen
+        done(out)
+    ''')
+    least = {(1024, 4, 4): 8, (256, 3, 4): 8, (256, 3, 3): 6, (1024, 4, 2): 6, (300, 2, 2): 4, (1024, 1, 1): 4, (16, 4, 4): 4}
+    for key, seen in r.items():
+        dims = tuple(int(v) for v in key.split()[:3])
+        for n, odd, ran in seen:
+            assert ("k_tube" in ran) == (n >= least[dims]), (key, n, odd, ran)
+            if "k_tube" in ran:
+                assert ran.count("k_update") == odd + n % 2 and ran.count("k_tube") == (1 if dims[0] == 16 else 2)
+            else:
+                assert ran == ["k_update"] * (n + odd)
