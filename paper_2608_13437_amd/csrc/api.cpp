@@ -248,7 +248,8 @@ struct cnsf_lattice {
   // several updates per launch: second array (unless one window holds the lattice) and windows
   void* tube_ws = nullptr;
   TubePlan tube;
-  bool tube_decided = false;
+  bool tube_decided = false, tube_wanted = false;
+  double tube_missed = 0.0;              // us that windows would have saved so far
   bool own_launch = false;               // the caller chose the launch shape of the update
   bool torn = false;                     // a pass was refused half way: the array holds no time level
 };
@@ -351,8 +352,9 @@ constexpr int64_t PAIR_STEPS = 4;
 // (224^3 1060 / 1180, 256^3 1530 / 1400, 288^3 2560 / 2550 to 2990, 320^3 2980 / 3000): slabs, the smaller.
 constexpr size_t pair_ws_whole(int storage) { return (size_t)(storage == CNSF_STORAGE_FP32 ? 2 : 8) << 30; }
 constexpr size_t PAIR_WS_SLABS = (size_t)2 << 30;
-// What making a workspace costs (us; 64^3 FP32, five steps: first call 208 without, 320 with; 4.5 GB 1.5 ms).
-constexpr double pair_ws_cost(size_t bytes) { return 100.0 + 3e-7 * (double)bytes; }
+// What making a workspace costs a call (us; first call with / without: 256 x 4 x 4 FP32, 1.6 MB, 37 / 35; 1024 x 4 x 4,
+// 6.4 MB, 70 / 40; 64^3, 103 MB, 320 / 208; 4.5 GB 1.5 ms).
+double ws_cost(size_t bytes) { return std::min(100.0, 5.0 + 4e-6 * (double)bytes) + 3e-7 * (double)bytes; }
 
 // Whether `L` makes n updates by paired passes.  The first call decides; the workspace is made (if it may be) by
 // the call with which pairs would have saved its cost, so that a short run does not pay for what it cannot use.
@@ -374,7 +376,7 @@ bool pair_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   }
   L->pair_missed += (double)n * L->pair.gain;
   size_t bytes = pair_workspace_bytes(L->g, L->p.storage, L->pair.split);
-  if (L->pair_missed < pair_ws_cost(bytes)) return false;
+  if (L->pair_missed < ws_cost(bytes)) return false;
   // what the free memory leaves of the plan (asking takes 30 us: not before it matters)
   const RelaxedCapture relaxed;
   size_t freeb = 0, total = 0;
@@ -394,18 +396,31 @@ bool pair_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
 // Whether `L` makes n updates by windows of several (tube.hip); decides and allocates like pair_ready.
 bool tube_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   if (L->own_launch) return false;
-  if (!L->tube_decided && may_alloc) {
+  if (!L->tube_decided) {
+    if (!may_alloc) return false;
     L->tube_decided = true;
-    const RelaxedCapture relaxed;
     int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) cus = 0;
-    if (cus > 0 && tube_plan(L->g, L->p.storage, cus, &L->tube) && L->tube.xw != (int)L->g.nx &&
-        hipMalloc(&L->tube_ws, L->bytes) != hipSuccess) {
-      (void)hipGetLastError();   // single updates then
-      L->tube_ws = nullptr;
-    }
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess)
+      (void)hipGetLastError();
+    else
+      L->tube_wanted = tube_plan(L->g, L->p.storage, cus, &L->tube);
   }
-  return n >= L->tube.least && (L->tube.xw == (int)L->g.nx || L->tube_ws != nullptr);
+  if (!L->tube_wanted || n < L->tube.least) return false;
+  if (L->tube.xw == (int)L->g.nx || L->tube_ws) return true;
+  if (!may_alloc) return false;
+  L->tube_missed += (double)n * L->tube.gain;
+  // a call that would capture a graph of single updates instead pays 125 us for that
+  const bool capture = L->g.ncells <= GRAPH_MAX_CELLS && n >= 2 * GRAPH_STEPS && !L->gexec;
+  if (L->tube_missed + (capture ? 125.0 : 0.0) < ws_cost(L->bytes)) return false;
+  const RelaxedCapture relaxed;
+  size_t freeb = 0, total = 0;
+  L->tube_wanted = hipMemGetInfo(&freeb, &total) == hipSuccess && L->bytes <= freeb / 8;
+  if (L->tube_wanted && hipMalloc(&L->tube_ws, L->bytes) != hipSuccess) {
+    L->tube_ws = nullptr;
+    L->tube_wanted = false;
+  }
+  if (!L->tube_wanted) (void)hipGetLastError();   // single updates then
+  return L->tube_wanted;
 }
 
 // Up to n updates from an even level by windows (an even number); *left: n less what was enqueued.  Windows

@@ -73,6 +73,7 @@ hipError_t launch_pair_batch(int storage, bool scaled, void* home, void* second,
 // long as the lattice takes any number, in place.
 struct TubePlan {
   int xw = 0, steps = 0, least = 4;
+  double gain = 0.0;   // us per update over single updates, by the plan's times
 };
 bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out);
 // `steps` (even) updates of a lattice at an even level, from src to dst (both laid out as the array).

@@ -167,7 +167,7 @@ bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
   if (cross > TUBE_THREADS / 4u) return false;
   const int most = TUBE_THREADS / (int)cross, nx = (int)g.nx;
   if (nx <= most) {
-    *out = TubePlan{nx, 1 << 20, 4};
+    *out = TubePlan{nx, 1 << 20, 4, 0.0};
     return true;
   }
   const bool fp32 = storage == 0;
@@ -183,10 +183,11 @@ bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
     const double t = (rounds * (8.0 + (fp32 ? 2.03 : 2.45) * s) + (fp32 ? 0.27 : 0.45) * mb) / s;
     if (t < best) {
       best = t;
-      *out = TubePlan{most, s, least};
+      *out = TubePlan{most, s, least, 0.0};
     }
   }
-  return best < (fp32 ? 4.0 + 9.5e-5 * g.ncells : 4.6 + 4.3e-5 * g.ncells);
+  out->gain = (fp32 ? 4.0 + 9.5e-5 * g.ncells : 4.6 + 4.3e-5 * g.ncells) - best;
+  return out->gain > 0.0;
 }
 
 template <int ST, int BC, bool SC>

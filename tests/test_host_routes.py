@@ -192,3 +192,45 @@ def test_short_calls_of_windowed_lattices(host):
                 assert ran.count("k_update") == odd + n % 2 and ran.count("k_tube") == (1 if dims[0] == 16 else 2)
             else:
                 assert ran == ["k_update"] * (n + odd)
+
+
+def test_workspace_of_windows_is_bounded_and_made_when_it_pays(host):
+    """The second array of the windows: within an eighth of the free memory, and made by the call
+    with which windows would have saved its cost (or which would capture a graph instead)."""
+    r = host('''
+        GB = 1 << 30
+        def held(prm, calls):
+            h0 = hip.double_held()
+            L = lattice(prm)
+            h1 = hip.double_held()
+            launched()
+            out = []
+            for n in calls:
+                cnsf.cnsf_step(L, n)
+                out.append([n, hip.double_held() - h1, "k_tube" in launched()])
+            nb = cnsf.cnsf_get_info(L)[2]
+            cnsf.cnsf_destroy(L)
+            return dict(nb=nb, calls=out, left=hip.double_held() - h0)
+        out = dict(
+            long=held(box(20000000, 1, 1), (4, 4)),
+            short_calls=held(box(1024, 4, 4), (10,) * 8), graph=held(box(1024, 4, 4), (64,)),
+            once=held(box(1024, 4, 4), (60,)), one_window=held(box(64, 1, 4), (4,)))
+        hip.double_memory(40 * GB)
+        out["long_tight"] = held(box(20000000, 1, 1), (4, 40, 400))
+        hip.double_memory(8 * GB)
+        out["tight"] = held(box(1024, 4, 4), (400,))
+        hip.double_memory(50000000)
+        out["very_tight"] = held(box(1024, 4, 4), (400, 400))
+        done(out)
+    ''')
+    for k, v in r.items():
+        assert v["left"] == 0, k
+        for n, taken, windows in v["calls"]:
+            assert taken in (0, v["nb"]), (k, v)
+    last = {k: v["calls"][-1][1:] for k, v in r.items()}
+    for k in ("long", "short_calls", "graph", "once", "tight"):
+        assert last[k] == [r[k]["nb"], True], (k, r[k])
+    for k in ("long_tight", "very_tight"):
+        assert last[k] == [0, False], (k, r[k])
+    assert last["one_window"] == [0, True]
+    assert r["short_calls"]["calls"][0][1:] == [0, False]      # ten updates do not pay for 6.4 MB
