@@ -316,9 +316,9 @@ int cnsf_batch_destroy(cnsf_batch* b);
 int cnsf_batch_set_state(cnsf_batch* b, int32_t j, const double* Q, int32_t where);
 /* Advance every member by n steps.  mode 0: one launch per step over all
  * members; mode 1: two steps per pass over memory where that is faster (the
- * first such call takes a second array of the batch's size, if that is within
- * 32 GiB and an eighth of the free device memory, and keeps it until
- * cnsf_batch_destroy; the stored populations are the same bit for bit), else
+ * call with which this would have saved the cost of it takes a second array of the
+ * batch's size, if that is within 32 GiB and an eighth of the free device memory,
+ * and keeps it until cnsf_batch_destroy; the stored populations are the same bit for bit), else
  * mode 0's launches replayed from a HIP graph of `graph_steps` steps (captured
  * on first use); mode 2: one launch per member per step (the sequential
  * baseline).  While the stream is being captured, mode 1 records no paired

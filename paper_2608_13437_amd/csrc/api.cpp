@@ -352,9 +352,6 @@ constexpr int64_t PAIR_STEPS = 4;
 // (224^3 1060 / 1180, 256^3 1530 / 1400, 288^3 2560 / 2550 to 2990, 320^3 2980 / 3000): slabs, the smaller.
 constexpr size_t pair_ws_whole(int storage) { return (size_t)(storage == CNSF_STORAGE_FP32 ? 2 : 8) << 30; }
 constexpr size_t PAIR_WS_SLABS = (size_t)2 << 30;
-// What making a workspace costs a call (us; first call with / without: 256 x 4 x 4 FP32, 1.6 MB, 37 / 35; 1024 x 4 x 4,
-// 6.4 MB, 70 / 40; 64^3, 103 MB, 320 / 208; 4.5 GB 1.5 ms).
-double ws_cost(size_t bytes) { return std::min(100.0, 5.0 + 4e-6 * (double)bytes) + 3e-7 * (double)bytes; }
 
 // Whether `L` makes n updates by paired passes.  The first call decides; the workspace is made (if it may be) by
 // the call with which pairs would have saved its cost, so that a short run does not pay for what it cannot use.

@@ -110,7 +110,9 @@ struct cnsf_batch {
   bool scaled = false;   // some member stores with a non-unit scale
   bool interleaved = false;  // component-major population layout
   // two updates per pass (pair.hip): second array and tables, decided at the first call that can use them
-  bool pair_decided = false;
+  bool pair_decided = false, pair_wanted = false;
+  double pair_gain = 0.0, pair_missed = 0.0;   // us per update over single ones; us that they would have saved so far
+  size_t pair_bytes = 0;
   void* pair_ws = nullptr;
   PairMember* dpair = nullptr;
   uint16_t* dpair_block = nullptr;   // member of every block
@@ -211,44 +213,60 @@ static void batch_drop_pairs(cnsf_batch* b) {
   b->dpair_block = nullptr;
 }
 
-// Whether the batch advances by paired passes; the first call decides and allocates.
-static bool batch_pair_ready(cnsf_batch* b) try {
-  if (b->pair_decided) return b->pair_ws != nullptr;
-  b->pair_decided = true;
-  const RelaxedCapture relaxed;
-  const size_t eb = elem_bytes(b->storage), n = b->m.size();
-  size_t freeb = 0, total = 0;
+// Whether the batch makes n steps by paired passes.  The first call decides; the second array is made by the
+// call with which pairs would have saved its cost (or, with `now`, at once).
+static bool batch_pair_ready(cnsf_batch* b, int64_t n, bool now) try {
+  if (b->pair_ws) return true;
+  if (b->pair_decided && !b->pair_wanted) return false;
+  const size_t eb = elem_bytes(b->storage), members = b->m.size();
   int cus = 0;
-  for (const Member& M : b->m)
-    if (M.g.cstride * eb > 0xFFFF0000ull) return false;   // dead lanes use offsets from there on
-  if (hipMemGetInfo(&freeb, &total) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
+  std::vector<PairMember> pm;
+  auto plan = [&] {
+    uint64_t elements = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    pm.resize(members);
+    const bool faster = pair_batch_plan(b->m.data(), (int)members, b->storage, cus, pm.data(), &b->pair_blocks,
+                                        &b->pair_threads, &elements, &b->pair_gain);
+    b->pair_bytes = elements * eb;
+    return faster;
+  };
+  if (!b->pair_decided) {
+    b->pair_decided = true;
+    b->pair_wanted = plan() && b->pair_bytes <= PAIR_BATCH_WS;
+    for (const Member& M : b->m)
+      if (M.g.cstride * eb > 0xFFFF0000ull) b->pair_wanted = false;   // dead lanes use offsets from there on
+    if (!b->pair_wanted) return false;
   }
-  std::vector<PairMember> pm(n);
-  uint64_t elements = 0;
-  if (!pair_batch_plan(b->m.data(), (int)n, b->storage, cus, pm.data(), &b->pair_blocks, &b->pair_threads, &elements) ||
-      elements * eb > std::min(PAIR_BATCH_WS, freeb / 8))
-    return false;
+  b->pair_missed += (double)n * b->pair_gain;
+  if (!now && b->pair_missed < ws_cost(b->pair_bytes)) return false;
+  if (pm.empty() && !plan()) return false;
   std::vector<uint16_t> owner(b->pair_blocks);
-  for (size_t j = 0; j < n; ++j) {
-    const uint32_t end = j + 1 < n ? pm[j + 1].block0 : b->pair_blocks;
+  for (size_t j = 0; j < members; ++j) {
+    const uint32_t end = j + 1 < members ? pm[j + 1].block0 : b->pair_blocks;
     std::fill(owner.begin() + pm[j].block0, owner.begin() + end, (uint16_t)j);
   }
-  hipError_t e = hipMalloc(&b->pair_ws, elements * eb);
-  if (e == hipSuccess) e = hipMalloc(&b->dpair, sizeof(PairMember) * n);
+  const RelaxedCapture relaxed;
+  size_t freeb = 0, total = 0;
+  hipError_t e = hipMemGetInfo(&freeb, &total);
+  if (e == hipSuccess && b->pair_bytes > freeb / 8) e = hipErrorOutOfMemory;
+  if (e == hipSuccess) e = hipMalloc(&b->pair_ws, b->pair_bytes);
+  if (e == hipSuccess) e = hipMalloc(&b->dpair, sizeof(PairMember) * members);
   if (e == hipSuccess) e = hipMalloc(&b->dpair_block, sizeof(uint16_t) * owner.size());
-  if (e == hipSuccess) e = hipMemcpyAsync(b->dpair, pm.data(), sizeof(PairMember) * n, hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(b->dpair, pm.data(), sizeof(PairMember) * members, hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->dpair_block, owner.data(), sizeof(uint16_t) * owner.size(), hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();   // single updates then
     batch_drop_pairs(b);
+    b->pair_wanted = false;
   }
   return b->pair_ws != nullptr;
 } catch (const std::bad_alloc&) {   // host memory for the tables: single steps then
+  b->pair_wanted = false;
   return b->pair_ws != nullptr;
 }
 
@@ -257,6 +275,7 @@ static void batch_refuse_pairs(cnsf_batch* b) {
   if (b->pair_ws) (void)hipStreamSynchronize(b->stream);
   batch_drop_pairs(b);
   b->pair_decided = true;
+  b->pair_wanted = false;
 }
 
 // n steps (a multiple of four) from an even level, forward and back.
@@ -464,7 +483,7 @@ int cnsf_batch_step(cnsf_batch* b, int64_t n, int32_t mode) {
     // paired passes, forward and back, of four updates
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (b->stream) (void)hipStreamIsCapturing(b->stream, &cap);
-    if (e == hipSuccess && left >= 4 && cap == hipStreamCaptureStatusNone && batch_pair_ready(b)) {
+    if (e == hipSuccess && left >= 4 && cap == hipStreamCaptureStatusNone && batch_pair_ready(b, left, false)) {
       e = batch_pair_steps(b, left / 4 * 4);
       left %= 4;
     }
@@ -625,7 +644,7 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
   // paired steps against the best shape of single ones (16-bit batches in a fast array: FP16 64 members
   // of 32^3 to 96^3 1.55 ms per step single and 1.59 paired, 1.87 and 1.64 in a plain array)
   int pairs = -1;
-  if (e == hipSuccess && batch_pair_ready(b)) {
+  if (e == hipSuccess && batch_pair_ready(b, 0, true)) {
     const int64_t n = (steps_per_trial + 3) / 4 * 4;
     e = batch_pair_steps(b, 4);
     if (e == hipSuccess) e = hipEventRecord(t0, b->stream);

@@ -31,6 +31,13 @@ hipError_t launch_moments(int storage, const void* pop, double* out, const Geom&
                           uint32_t cell0, uint32_t nslab, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 
+// What making a workspace costs a call (us; first call with / without: 256 x 4 x 4 FP32, 1.6 MB, 37 / 35; 1024 x 4 x 4,
+// 6.4 MB, 70 / 40; 64^3, 103 MB, 320 / 208; 4.5 GB 1.5 ms).
+inline double ws_cost(size_t bytes) {
+  const double mb = 1e-6 * (double)bytes;
+  return (mb < 24.0 ? 5.0 + 4.0 * mb : 100.0) + 0.3 * mb;
+}
+
 // Two updates in one pass (pair.hip): planes of the workspace, planes per launch, planes per block,
 // columns of a tile along x and y.
 struct PairPlan {
@@ -62,8 +69,9 @@ struct PairMember {
   int tx, ty, ntx, ncol, chunk;
   uint64_t offset, cstride;
 };
+// `gain`: us per update over single updates, by the plan's times.
 bool pair_batch_plan(const Member* m, int n, int storage, int cus, PairMember* out, uint32_t* blocks, int* threads,
-                     uint64_t* elements);
+                     uint64_t* elements, double* gain);
 hipError_t launch_pair_batch(int storage, bool scaled, void* home, void* second, const Member* members,
                              const PairMember* pm, const uint16_t* block_member, uint32_t blocks, int threads, bool back,
                              hipStream_t s);

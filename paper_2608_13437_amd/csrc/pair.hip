@@ -609,7 +609,7 @@ static double batch_cut(const Member* m, int n, int storage, int height, PairMem
 // 0.96, 0.94.  Few members: 8 of mixed sizes FP16 0.16 / 0.15, BF16 0.29 / 0.29 and three BF16 0.17 /
 // 0.20 are left to single updates.
 bool pair_batch_plan(const Member* m, int n, int storage, int cus, PairMember* out, uint32_t* blocks, int* threads,
-                     uint64_t* elements) {
+                     uint64_t* elements, double* gain) {
   double best = 1e300, cells = 0.0, longest = 0.0;
   int height = 0;
   for (const int h : {12, 16, 24, 32, 48}) {
@@ -624,7 +624,8 @@ bool pair_batch_plan(const Member* m, int n, int storage, int cus, PairMember* o
   batch_cut(m, n, storage, height, out, blocks, threads, &longest);
   *elements = out[n - 1].offset + NC * out[n - 1].cstride;
   for (int j = 0; j < n; ++j) cells += m[j].g.ncells;
-  return best < 2e-3 * (storage == 0 ? 0.155 : 0.08) * cells;
+  *gain = 1e-3 * (storage == 0 ? 0.155 : 0.08) * cells - 0.5 * best;
+  return *gain > 0.0;
 }
 
 hipError_t launch_pair_batch(int storage, bool scaled, void* home, void* second, const Member* members,

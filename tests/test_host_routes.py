@@ -234,3 +234,30 @@ def test_workspace_of_windows_is_bounded_and_made_when_it_pays(host):
         assert last[k] == [0, False], (k, r[k])
     assert last["one_window"] == [0, True]
     assert r["short_calls"]["calls"][0][1:] == [0, False]      # ten updates do not pay for 6.4 MB
+
+
+def test_second_array_of_batches_is_made_when_it_pays(host):
+    """A short call of the graph mode neither allocates nor waits for what it cannot use."""
+    r = host('''
+        lib = cnsf.library()
+        def held(prms, calls):
+            h = batch(prms)
+            h1 = hip.double_held()
+            launched()
+            out = []
+            for n in calls:
+                assert lib.cnsf_batch_step(h, n, 1) == 0
+                out.append([hip.double_held() > h1, "k_pair_batch" in launched()])
+            lib.cnsf_batch_destroy(h)
+            return out
+        some = [box(64, 64, 64, storage=1)] * 16
+        out = dict(short=held(some, (4,) * 10), once=held(some, (80,)), many=held([box(96, 96, 96)] * 48, (4,)))
+        hip.double_memory(64 ** 3 * 98 * 2 * 16 * 6)
+        out["tight"] = held(some, (80, 80))
+        done([out, hip.double_held()])
+    ''')
+    out, left = r
+    assert left == 0
+    assert out["short"][0] == [False, False] and out["short"][-1] == [True, True], out
+    assert out["once"] == [[True, True]] and out["many"] == [[True, True]], out
+    assert out["tight"] == [[False, False]] * 2, out
