@@ -335,7 +335,9 @@ int cnsf_batch_get_launch(const cnsf_batch* b, int32_t* block, int32_t* tile, in
 /* Time candidate launch shapes with HIP events and keep the fastest, and single steps if
  * mode 1's paired ones (which need their second array for this) are not faster; results
  * are cached in the JSON file `cache_path` (may be NULL) keyed by the batch's
- * shape signature. */
+ * shape signature (storage and sorted cell counts).  Single steps are kept there only
+ * where they led by more than a fifth, and read only by batches of the same members'
+ * edges, scaled codes and component spacing; others take pairs by their plan. */
 int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per_trial);
 
 #ifdef __cplusplus

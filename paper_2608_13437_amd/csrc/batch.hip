@@ -554,8 +554,30 @@ static std::string batch_signature(const cnsf_batch* b) {
   return os.str();
 }
 
-// `pairs`: 0 if single steps were measured faster than paired ones, 1 if not, -1 if the entry does not say.
-static bool cache_lookup(const char* path, const std::string& key, int& block, int& tile, int& grid, int& pairs) {
+// What the choice between single and paired steps hangs on beside the sizes: every member's edges, scaled codes,
+// and the distance of the component runs.
+static std::string batch_shape(const cnsf_batch* b) {
+  uint64_t h = 1469598103934665603ull;
+  auto mix = [&h](uint64_t v) {
+    h ^= v;
+    h *= 1099511628211ull;
+  };
+  mix(b->scaled);
+  mix(b->interleaved ? b->m[0].g.cstride : 0);
+  for (const auto& M : b->m) {
+    mix(M.g.nx);
+    mix(M.g.ny);
+    mix(M.g.nz);
+  }
+  char s[17];
+  snprintf(s, sizeof s, "%016llx", (unsigned long long)h);
+  return s;
+}
+
+// `pairs`: 0 if single steps were measured clearly faster than paired ones for a batch of this `shape`, 1 if not, -1
+// if the entry does not say (or speaks of other members of the same cell counts).
+static bool cache_lookup(const char* path, const std::string& key, const std::string& shape, int& block, int& tile,
+                         int& grid, int& pairs) {
   if (!path) return false;
   std::ifstream in(path);
   if (!in) return false;
@@ -564,12 +586,16 @@ static bool cache_lookup(const char* path, const std::string& key, int& block, i
   const std::string s = ss.str();
   const size_t pos = s.find("\"" + key + "\"");
   if (pos == std::string::npos) return false;
-  pairs = -1;
-  return sscanf(s.c_str() + pos + key.size() + 2, " : {\"block\": %d, \"tile\": %d, \"grid\": %d, \"pairs\": %d}", &block,
-                &tile, &grid, &pairs) >= 3;
+  char of[17] = "";
+  const int got = sscanf(s.c_str() + pos + key.size() + 2,
+                         " : {\"block\": %d, \"tile\": %d, \"grid\": %d, \"pairs\": %d, \"shape\": \"%16[0-9a-f]\"}", &block,
+                         &tile, &grid, &pairs, of);
+  if (got < 5 || shape != of) pairs = -1;
+  return got >= 3;
 }
 
-static void cache_store(const char* path, const std::string& key, int block, int tile, int grid, int pairs) {
+static void cache_store(const char* path, const std::string& key, const std::string& shape, int block, int tile, int grid,
+                        int pairs) {
   if (!path) return;
   std::string body;
   {
@@ -581,8 +607,8 @@ static void cache_store(const char* path, const std::string& key, int block, int
     }
   }
   char entry[256];
-  snprintf(entry, sizeof entry, "\"%s\": {\"block\": %d, \"tile\": %d, \"grid\": %d, \"pairs\": %d}", key.c_str(), block,
-           tile, grid, pairs);
+  snprintf(entry, sizeof entry, "\"%s\": {\"block\": %d, \"tile\": %d, \"grid\": %d, \"pairs\": %d, \"shape\": \"%s\"}",
+           key.c_str(), block, tile, grid, pairs, shape.c_str());
   const size_t close = body.rfind('}');
   if (body.empty() || close == std::string::npos) {
     body = std::string("{\n  ") + entry + "\n}\n";
@@ -601,9 +627,9 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
   if (steps_per_trial < 2) steps_per_trial = 2;
   steps_per_trial += steps_per_trial % 2;
   (void)hipSetDevice(b->device);
-  const std::string key = batch_signature(b);
+  const std::string key = batch_signature(b), shape = batch_shape(b);
   int bb, tt, gg, pp;
-  if (cache_lookup(cache_path, key, bb, tt, gg, pp)) {
+  if (cache_lookup(cache_path, key, shape, bb, tt, gg, pp)) {
     if (pp == 0) batch_refuse_pairs(b);
     return cnsf_batch_set_launch(b, bb, tt, gg, b->graph_steps);
   }
@@ -642,7 +668,9 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
     }
   }
   // paired steps against the best shape of single ones (16-bit batches in a fast array: FP16 64 members
-  // of 32^3 to 96^3 1.55 ms per step single and 1.59 paired, 1.87 and 1.64 in a plain array)
+  // of 32^3 to 96^3 1.55 ms per step single and 1.59 paired, 1.87 and 1.64 in a plain array).  The array's
+  // memory moves single steps by that fifth and may turn the verdict, so the file, which outlives the array, is
+  // told of single steps only where they lead by more.
   int pairs = -1;
   if (e == hipSuccess && batch_pair_ready(b, 0, true)) {
     const int64_t n = (steps_per_trial + 3) / 4 * 4;
@@ -653,8 +681,13 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
     if (e == hipSuccess) e = hipEventSynchronize(t1);
     float ms = 0.f;
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, t0, t1);
-    pairs = ms / (float)n < best / (float)steps_per_trial;
-    if (e == hipSuccess && !pairs) batch_refuse_pairs(b);
+    const float paired = ms / (float)n, single = best / (float)steps_per_trial;
+    if (e == hipSuccess && paired >= single) {
+      batch_refuse_pairs(b);
+      if (paired > 1.2f * single) pairs = 0;
+    } else {
+      pairs = 1;
+    }
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
@@ -664,7 +697,7 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
   b->parity = parity0;
   if (e != hipSuccess) return hip_fail(e, "autotune");
   if (int r = cnsf_batch_set_launch(b, bestc.block, bestc.tile, bestc.grid, b->graph_steps)) return r;
-  cache_store(cache_path, key, bestc.block, bestc.tile, bestc.grid, pairs);
+  cache_store(cache_path, key, shape, bestc.block, bestc.tile, bestc.grid, pairs);
   return CNSF_OK;
 }
 

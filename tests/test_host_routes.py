@@ -261,3 +261,43 @@ def test_second_array_of_batches_is_made_when_it_pays(host):
     assert out["short"][0] == [False, False] and out["short"][-1] == [True, True], out
     assert out["once"] == [[True, True]] and out["many"] == [[True, True]], out
     assert out["tight"] == [[False, False]] * 2, out
+
+
+def test_cached_verdict_on_pairs_belongs_to_its_batch(host, tmp_path):
+    """The autotuner's file: single steps for a batch of the same members if they led by more than
+    arrays differ; other members of the same cell counts, other strides or scales decide for
+    themselves, and an entry without the members' shape says nothing about pairs."""
+    r = host(f'''
+        lib = cnsf.library()
+        cube, flat = [box(64, 64, 64, storage=1)] * 32, [box(128, 64, 32, storage=1)] * 32
+        def pairs_run(prms, path, tune=True):
+            h = batch(prms)
+            if tune:
+                assert lib.cnsf_batch_autotune(h, path, 4) == 0
+            launched()
+            assert lib.cnsf_batch_step(h, 400, 1) == 0
+            out = "k_pair_batch" in launched()
+            lib.cnsf_batch_destroy(h)
+            return out
+        out = dict()
+        for name, cost in dict(clear=10.0, close=2.2, faster=1.0).items():   # ms per pair of steps; single steps 1
+            path = ({str(tmp_path)!r} + "/" + name).encode()
+            hip.double_cost(b"k_pair_batch", cost)
+            first = pairs_run(cube, path)
+            again = pairs_run(cube, path)
+            other = pairs_run(flat, path)
+            scaled = pairs_run([dict(cube[0], storage_scale=[0.5] * 14)] * 32, path)
+            text = open(path).read()
+            import re
+            open(path, "w").write(re.sub(', "shape": "[0-9a-f]*"', "", text))
+            old = pairs_run(cube, path)
+            open(path, "w").write(re.sub(', "pairs".*}}', "}}", text))
+            oldest = pairs_run(cube, path)
+            out[name] = [first, again, other, scaled, old, oldest, text]
+        done(out)
+    ''')
+    assert r["clear"][:6] == [False, False, True, True, True, True], r
+    assert r["close"][:6] == [False, True, True, True, True, True], r
+    assert r["faster"][:6] == [True] * 6, r
+    for v in r.values():
+        json.loads(v[6])
