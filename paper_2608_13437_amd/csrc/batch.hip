@@ -633,9 +633,17 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
     if (pp == 0) batch_refuse_pairs(b);
     return cnsf_batch_set_launch(b, bb, tt, gg, b->graph_steps);
   }
+  // paired steps are among the trials: their second array is asked for while the memory of the copy is still free
+  const bool had_pairs = b->pair_ws != nullptr;
+  (void)batch_pair_ready(b, 0, true);
   // trial steps change the state: keep a copy and restore it afterwards
   void* save = nullptr;
   hipError_t e = hipMalloc(&save, b->bytes);
+  if (e != hipSuccess && !had_pairs && b->pair_ws) {
+    (void)hipGetLastError();
+    batch_drop_pairs(b);   // left to a later call
+    e = hipMalloc(&save, b->bytes);
+  }
   if (e != hipSuccess) return fail(CNSF_E_NOMEM, "autotune copy of %zu bytes: %s", b->bytes, hipGetErrorString(e));
   e = hipMemcpyAsync(save, b->base, b->bytes, hipMemcpyDeviceToDevice, b->stream);
   int ncu = 256;
@@ -672,7 +680,7 @@ int cnsf_batch_autotune(cnsf_batch* b, const char* cache_path, int32_t steps_per
   // memory moves single steps by that fifth and may turn the verdict, so the file, which outlives the array, is
   // told of single steps only where they lead by more.
   int pairs = -1;
-  if (e == hipSuccess && batch_pair_ready(b, 0, true)) {
+  if (e == hipSuccess && b->pair_ws) {
     const int64_t n = (steps_per_trial + 3) / 4 * 4;
     e = batch_pair_steps(b, 4);
     if (e == hipSuccess) e = hipEventRecord(t0, b->stream);

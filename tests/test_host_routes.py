@@ -301,3 +301,35 @@ def test_cached_verdict_on_pairs_belongs_to_its_batch(host, tmp_path):
     assert r["faster"][:6] == [True] * 6, r
     for v in r.values():
         json.loads(v[6])
+
+
+def test_autotuner_asks_for_its_second_array_before_its_copy(host):
+    """The copy of the state that the trials need must not make the second array seem too large:
+    free memory of 8.5 arrays holds an eighth before the copy, not after it."""
+    r = host('''
+        lib = cnsf.library()
+        prms = [box(64, 64, 64, storage=1)] * 32
+        nb = 32 * 64 ** 3 * 98 * 2
+        out = []
+        for room in (8.5, 7.5):
+            hip.double_memory(int((1 + room) * nb))
+            h = batch(prms)
+            assert lib.cnsf_batch_autotune(h, None, 4) == 0
+            launched()
+            assert lib.cnsf_batch_step(h, 8, 1) == 0
+            out.append("k_pair_batch" in launched())
+            lib.cnsf_batch_destroy(h)
+        # an array much wider than its members' slots: the copy of it comes first
+        hip.double_memory(21 * nb)
+        wide = C.c_void_p()
+        hip.hipMalloc(C.byref(wide), C.c_size_t(10 * nb))
+        h = C.c_void_p()
+        ps = (cnsf.cnsf_params * 32)(*[cnsf.make_params(p) for p in prms])
+        assert lib.cnsf_batch_create(ps, 32, wide, 10 * nb, None, C.byref(h)) == 0
+        assert lib.cnsf_batch_autotune(h, None, 4) == 0
+        launched()
+        assert lib.cnsf_batch_step(h, 8, 1) == 0
+        out.append("k_pair_batch" in launched())
+        done(out)
+    ''')
+    assert r == [True, False, True]
