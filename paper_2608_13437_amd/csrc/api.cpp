@@ -520,8 +520,10 @@ int cnsf_create(const cnsf_params* p, void* dev_buf, size_t bytes, void* stream,
   L->stream = (hipStream_t)stream;
   L->bytes = need;
   L->lc = default_launch(p->storage);
-  L->run = lattice_launch(p->storage, L->g.ncells);
   (void)hipGetDevice(&L->device);
+  int cus = 256;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) (void)hipGetLastError();
+  L->run = lattice_launch(p->storage, L->g.ncells, cus);
   hipError_t e;
   if (dev_buf) {
     L->pop = dev_buf;

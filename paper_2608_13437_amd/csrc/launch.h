@@ -18,8 +18,8 @@ struct Launch {
 };
 // Shape measured best on MI355X for each storage type (512^3 Taylor-Green).
 Launch default_launch(int storage);
-// Shape in which a lattice of ncells is launched unless its caller set one.
-Launch lattice_launch(int storage, uint64_t ncells);
+// Shape in which a lattice of ncells is launched on `cus` compute units unless its caller set one.
+Launch lattice_launch(int storage, uint64_t ncells, int cus);
 
 hipError_t launch_update(int storage, void* pop, const Geom& g, const Phys& ph, const Codec& cd, int parity,
                          const Launch& lc, hipStream_t s);

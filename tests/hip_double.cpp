@@ -20,6 +20,7 @@ std::map<const void*, std::string> g_names;
 std::vector<Launched> g_log;
 std::map<uintptr_t, size_t> g_live;
 uintptr_t g_next = (uintptr_t)1 << 44;
+int g_cus = 256;
 size_t g_free = (size_t)288 << 30;
 long g_fail = -1;                  // launches until one is refused
 hipError_t g_error = hipSuccess;   // what hipGetLastError returns next
@@ -45,6 +46,8 @@ extern "C" {
 size_t double_launches() { return g_log.size(); }
 const char* double_name(size_t i) { return g_log[i].name.c_str(); }
 unsigned double_block(size_t i) { return g_log[i].block.x; }
+unsigned double_grid(size_t i) { return g_log[i].grid.x; }
+void double_cus(int n) { g_cus = n; }
 void double_forget() { g_log.clear(); }
 void double_refuse(long after) { g_fail = after; }
 void double_cost(const char* name, double ms) { g_cost[name] = ms; }
@@ -142,7 +145,7 @@ hipError_t hipGetDevice(int* d) {
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
-  *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 0;
+  *v = a == hipDeviceAttributeMultiprocessorCount ? g_cus : 0;
   return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {

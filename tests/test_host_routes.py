@@ -24,7 +24,7 @@ import paper_2608_13437_amd as cnsf
 import workloads as W
 hip.double_launches.restype = hip.double_held.restype = C.c_size_t
 hip.double_name.restype = C.c_char_p
-hip.double_name.argtypes = hip.double_block.argtypes = [C.c_size_t]
+hip.double_name.argtypes = hip.double_block.argtypes = hip.double_grid.argtypes = [C.c_size_t]
 hip.double_refuse.argtypes = [C.c_long]
 hip.double_memory.argtypes = [C.c_size_t]
 hip.double_cost.argtypes = [C.c_char_p, C.c_double]
@@ -48,6 +48,11 @@ def status(f, *a):
         return 0
     except cnsf.CnsfError as e:
         return e.status
+
+def shape():
+    """Threads per block and blocks of the last launch."""
+    i = hip.double_launches() - 1
+    return [hip.double_block(i), hip.double_grid(i)]
 
 def launched():
     """Names of the kernels launched since the last call of this, in order."""
@@ -333,3 +338,22 @@ def test_autotuner_asks_for_its_second_array_before_its_copy(host):
         done(out)
     ''')
     assert r == [True, False, True]
+
+
+def test_launch_shapes_follow_the_device(host):
+    """FP16 lattices of three to four 256-cell blocks per CU are launched as 512-cell tiles: the
+    line lies where the device's CUs put it."""
+    r = host('''
+        out = []
+        for cus in (128, 228, 256, 304):
+            hip.double_cus(cus)
+            for n in (50, 58, 59, 64, 65, 66, 70):
+                L = lattice(box(n, n, n, storage=1))
+                cnsf.cnsf_step(L, 1)
+                out.append([cus, n, *shape()])
+        done(out)
+    ''')
+    for cus, n, block, grid in r:
+        blocks = (n ** 3 + 255) // 256
+        tile = 512 if 3 * cus < blocks <= 4 * cus else 256
+        assert block == 256 and grid == (n ** 3 + tile - 1) // tile, (cus, n)
