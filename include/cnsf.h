@@ -283,10 +283,9 @@ int cnsf_hbm_copy(void* dst, const void* src, size_t bytes, void* stream);
  * that many blocks striding over the tiles; xcd_remap gives each of the 8 XCDs
  * one contiguous span of tiles.  block: 64..256 in steps of 64 (the kernels are
  * compiled for at most 256).  Defaults are the shapes measured fastest on
- * MI355X for the lattice's storage type; until this call lattices of few cells
- * (and FP16 ones within the last-level cache) are launched in shapes of their
- * own size, while cnsf_get_launch reports the storage type's.  After this call cnsf_step makes
- * single updates only, in this shape. */
+ * MI355X for the lattice's storage type and size; cnsf_get_launch reports the
+ * shape in which single updates run.  After cnsf_set_launch, of whatever shape,
+ * cnsf_step makes single updates only. */
 int cnsf_set_launch(cnsf_lattice* lat, int32_t block, int32_t tile, int32_t grid, int32_t xcd_remap);
 int cnsf_get_launch(const cnsf_lattice* lat, int32_t* block, int32_t* tile, int32_t* grid, int32_t* xcd_remap);
 

@@ -228,8 +228,7 @@ struct cnsf_lattice {
   int device = 0;
   int64_t step = 0;
   int parity = 0;
-  Launch lc;                          // as set or, for the lattice's storage type, the default
-  Launch run;                         // as launched
+  Launch run;                         // launch shape: by storage type and size, or as set
   int* dflag = nullptr;               // device error flag
   DiagPartial* partials = nullptr;    // diagnostics block partials
   DiagPartial* result = nullptr;      // two totals, in pinned host memory that the final reduction writes
@@ -519,7 +518,6 @@ int cnsf_create(const cnsf_params* p, void* dev_buf, size_t bytes, void* stream,
   L->cd = derive_codec(p, L->phd);
   L->stream = (hipStream_t)stream;
   L->bytes = need;
-  L->lc = default_launch(p->storage);
   (void)hipGetDevice(&L->device);
   int cus = 256;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device) != hipSuccess) (void)hipGetLastError();
@@ -577,11 +575,10 @@ int cnsf_set_launch(cnsf_lattice* L, int32_t block, int32_t tile, int32_t grid, 
   if (block < 64 || block > 256 || block % 64) return fail(CNSF_E_INVALID, "block %d not a multiple of 64 in [64, 256]", block);
   if (tile < block || tile % block) return fail(CNSF_E_INVALID, "tile %d must be a multiple of block %d", tile, block);
   if (grid < 0) return fail(CNSF_E_INVALID, "grid %d < 0", grid);
-  L->lc.block = block;
-  L->lc.tile = tile;
-  L->lc.grid = grid;
-  L->lc.remap = xcd_remap ? 1 : 0;
-  L->run = L->lc;
+  L->run.block = block;
+  L->run.tile = tile;
+  L->run.grid = grid;
+  L->run.remap = xcd_remap ? 1 : 0;
   L->own_launch = true;
   drop_graph(L);   // the captured updates carry the old shape
   return CNSF_OK;
@@ -975,10 +972,10 @@ int cnsf_spectrum(cnsf_lattice* L, double* E, int32_t nshells, int32_t where) {
 
 int cnsf_get_launch(const cnsf_lattice* L, int32_t* block, int32_t* tile, int32_t* grid, int32_t* xcd_remap) {
   if (!L) return fail(CNSF_E_INVALID, "lattice is NULL");
-  if (block) *block = L->lc.block;
-  if (tile) *tile = L->lc.tile;
-  if (grid) *grid = L->lc.grid;
-  if (xcd_remap) *xcd_remap = L->lc.remap;
+  if (block) *block = L->run.block;
+  if (tile) *tile = L->run.tile;
+  if (grid) *grid = L->run.grid;
+  if (xcd_remap) *xcd_remap = L->run.remap;
   return CNSF_OK;
 }
 

@@ -91,3 +91,32 @@ def test_readouts_of_many_lattices_share_pinned_pages():
         assert np.allclose(m, (1.0 + j) * mass, rtol=1e-5, atol=0.0), j
     for L in made.values():
         L.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz,storage,bc", CASES)
+def test_own_shape_equals_shape_of_large_lattices(nx, ny, nz, storage, bc):
+    """The shape by size against the one that large lattices of the storage type run in."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2608_13437_amd as cnsf
+    print(f"case {nx}x{ny}x{nz} storage {storage} ends {bc}", flush=True)
+    c = W.smooth_random_case(nx, ny, nz)
+    end = W.uniform_state(1.0, (0.0, 0.0, 0.0), 1.0, c.params["gamma"])
+    prm = dict(c.params, storage=storage, bc_x=bc, wall_u=[[0.0, 0.1, -0.05], [0.0, 0.2, 0.1]], wall_T=[0.0, 1.1],
+               Q_left=end, Q_right=end)
+    a, b = cnsf.Lattice(prm), cnsf.Lattice(prm)
+    for L in (a, b):
+        L.set_state(c.Q0)
+    large = (256, 512, 0, 0) if storage == F16 else (256, 256, 0, 1)
+    b.set_launch(*large)
+    assert b.get_launch() == large
+    for n in (1, 3, 2):
+        a.step(n)
+        b.step(n)
+        assert torch.equal(a.buf, b.buf)
+        a.step_diagnostics(1)
+        b.step_diagnostics(1)
+        assert torch.equal(a.buf, b.buf)
+    a.close()
+    b.close()

@@ -357,3 +357,22 @@ def test_launch_shapes_follow_the_device(host):
         blocks = (n ** 3 + 255) // 256
         tile = 512 if 3 * cus < blocks <= 4 * cus else 256
         assert block == 256 and grid == (n ** 3 + tile - 1) // tile, (cus, n)
+
+
+def test_reported_launch_shape_is_the_one_that_runs(host):
+    r = host('''
+        out = []
+        for n, storage in ((16, 0), (32, 1), (46, 2), (48, 0), (48, 1), (64, 1), (80, 1), (110, 1), (64, 2)):
+            L = lattice(box(n, n, n, storage=storage))
+            for shape_set in (None, "same", (128, 256, 0, 0)):
+                before = cnsf.cnsf_get_launch(L)
+                if shape_set:
+                    cnsf.cnsf_set_launch(L, *(before if shape_set == "same" else shape_set))
+                said = cnsf.cnsf_get_launch(L)
+                cnsf.cnsf_step(L, 1)
+                out.append([n, storage, shape_set == "same" and before != said, said, shape()])
+        done(out)
+    ''')
+    for n, storage, moved, (block, tile, grid, _), ran in r:
+        assert not moved and grid == 0
+        assert ran == [block, (n ** 3 + tile - 1) // tile], (n, storage)
