@@ -25,3 +25,24 @@ def test_traffic_is_reported_only_for_the_current_kernel_sources(tmp_path, monke
     assert bench.traffic_entry("fp16", 8.9) is None                      # storage not profiled
     path.write_text(json.dumps({"kernel_hash": "0" * 16, "fp32": {"bytes_per_launch": 123}}))
     assert bench.traffic_entry("fp32", 17.5) is None                     # kernel changed since
+
+
+def test_timed_steps_start_at_an_even_level_after_a_call_of_their_length():
+    """One-step calls leave the lattice at any level; the paired passes of the timed call need an even
+    one and their workspace, which a call from an odd level of too few steps does not make."""
+    class L:
+        def __init__(self, at):
+            self.at, self.calls = at, []
+
+        def info(self):
+            return self.at, self.at % 2, 0
+
+        def step(self, n):
+            self.calls.append(n)
+            self.at += n
+
+    for at in range(4):
+        for steps in (1, 4, 5, 20, 21):
+            lat = L(at)
+            bench.warm_steps(lat, steps)
+            assert lat.at % 2 == 0 and lat.calls[0] - at % 2 >= max(4, steps - 1), (at, steps, lat.calls)
