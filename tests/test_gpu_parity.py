@@ -665,6 +665,48 @@ def test_graph_replayed_steps_match_single_launches(storage):
     B.close()
 
 
+# lattices whose long calls replay a graph of single updates: between ends along x, and those for
+# which paired passes are not faster
+REPLAYED = [((40, 24, 18), "walls", 0), ((33, 17, 21), "noslip", 1), ((48, 48, 48), "periodic", 0),
+            ((32, 32, 32), "periodic", 2), ((64, 64, 64), "periodic", 1)]
+# launch shape of either lattice before its second and fourth call
+RESHAPED = {1: (128, 256, 0, False), 3: (64, 64, 512, True)}
+
+
+def replayed_params(dims, ends, storage):
+    bc = dict(periodic=W.BC_PERIODIC, walls=W.BC_WALL, noslip=W.BC_NOSLIP)[ends]
+    return dict(W.random_params(*dims), storage=storage, bc_x=bc, wall_u=[[0.0, 0.1, -0.05], [0.0, 0.2, 0.1]],
+                wall_T=[0.0, 1.1])
+
+
+@pytest.mark.parametrize("dims,ends,storage", REPLAYED)
+def test_graph_of_updates_is_captured_anew_after_a_shape_change(dims, ends, storage):
+    """Calls of 64 updates and more, in the default shape and in two others: every replay leaves
+    the populations of one launch per step, with odd levels and eager work between."""
+    cnsf = _cnsf()
+    import torch
+    prm = replayed_params(dims, ends, storage)
+    Q = W.smooth_random_case(*dims, seed=8).Q0
+    A, B = cnsf.Lattice(prm), cnsf.Lattice(prm)
+    A.set_state(Q)
+    B.set_state(Q)
+    for rep, n in enumerate((70, 64, 101, 96)):
+        if rep in RESHAPED:
+            A.set_launch(*RESHAPED[rep])
+            B.set_launch(*RESHAPED[rep])
+        log(f"case {dims} {ends} storage {storage}: call {rep} of {n} steps (parity {A.info()[1]})")
+        A.step(n)
+        for _ in range(n):
+            B.step(1)
+        torch.cuda.synchronize()
+        assert torch.equal(A.buf, B.buf), rep
+        A.step(1)
+        B.step(1)
+    assert bool(torch.isfinite(A.moments(device=True)).all())
+    A.close()
+    B.close()
+
+
 def test_steps_captured_by_the_caller_replay_exactly():
     """A caller that captures its own stream around cnsf_step gets the plain
     launches in its graph (the library's own replay is skipped while the

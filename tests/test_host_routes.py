@@ -376,3 +376,27 @@ def test_reported_launch_shape_is_the_one_that_runs(host):
     for n, storage, moved, (block, tile, grid, _), ran in r:
         assert not moved and grid == 0
         assert ran == [block, (n ** 3 + tile - 1) // tile], (n, storage)
+
+
+def test_replayed_lattices_capture_anew_after_a_shape_change(host):
+    """The lattices of the bitwise test on the GPU do replay a graph, and a new one in a new shape."""
+    import test_gpu_parity as g
+    r = host(f'''
+        out = []
+        for prm in {[g.replayed_params(*c) for c in g.REPLAYED]!r}:
+            L = lattice(prm)
+            for rep, n in enumerate((70, 64, 101, 96)):
+                s = {g.RESHAPED!r}.get(rep)
+                if s:
+                    cnsf.cnsf_set_launch(L, *s)
+                cnsf.cnsf_step(L, n)
+                names = launched()
+                out.append([rep, names.count("capture"), names.count("graph"), n, names.count("k_update"), s])
+                cnsf.cnsf_step(L, 1)
+                launched()
+        done(out)
+    ''')
+    assert len(r) == 4 * len(g.REPLAYED)
+    for rep, captures, replays, n, updates, s in r:
+        assert captures == (rep in (0, 1, 3)), (rep, captures)
+        assert replays >= 1 and updates == 32 * captures + n - 32 * replays, (rep, replays, updates)
