@@ -89,6 +89,43 @@ def test_paired_passes_equal_single_updates(nx, ny, nz, storage, scale, calls):
     b.close()
 
 
+# nx, ny, nz, storage, viscosity law and its parameter, steps per call: the power law of the run driver and the
+# bench, and constant viscosity (the cases above have Sutherland's law)
+LAWS = [
+    (96, 96, 96, W.STORAGE_FP32, W.VISC_POWER, 0.76, (5, 8, 6)),
+    (128, 128, 128, W.STORAGE_FP16, W.VISC_POWER, 0.76, (9, 8)),
+    (128, 126, 128, W.STORAGE_BF16, W.VISC_POWER, 1.3, (8, 9)),
+    (192, 192, 192, W.STORAGE_FP32, W.VISC_POWER, 0.76, (4, 5)),
+    (100, 96, 97, W.STORAGE_FP32, W.VISC_CONST, 0.0, (7, 8)),
+]
+
+
+@pytest.mark.parametrize("nx,ny,nz,storage,law,param,calls", LAWS)
+def test_paired_passes_of_other_viscosity_laws(nx, ny, nz, storage, law, param, calls):
+    import torch
+    cnsf = _cnsf()
+    prm = dict(W.random_params(nx, ny, nz, seed=4), storage=storage, visc_law=law, visc_param=param)
+    print(f"case {nx}x{ny}x{nz} storage {storage} law {law} calls {calls}", flush=True)
+    Q = _state(prm, 23)
+    a, b = cnsf.Lattice(prm), cnsf.Lattice(prm)
+    a.set_state(Q)
+    b.set_state(Q)
+    del Q
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    for n in calls:
+        b.step(n)
+    torch.cuda.synchronize()
+    taken = free0 - torch.cuda.mem_get_info()[0]
+    for _ in range(sum(calls)):
+        a.step(1)
+    assert taken >= a.nbytes // 32, f"single updates ran: {taken} bytes taken"
+    assert torch.equal(a.buf, b.buf)
+    assert bool(torch.isfinite(b.moments(device=True)).all())
+    a.close()
+    b.close()
+
+
 def test_paired_passes_give_their_workspace_back():
     import torch
     cnsf = _cnsf()
@@ -142,4 +179,40 @@ def test_first_steps_beside_a_capture_on_another_stream(kind):
     assert torch.equal(a.buf, b.buf)
     del g
     a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("kind", ["pairs", "windows", "batch"])
+def test_workspace_is_made_beside_a_capture_on_another_stream(kind):
+    """As above, with lattices whose workspace shows in the free memory: it is made while the other
+    stream captures."""
+    import torch
+    cnsf = _cnsf()
+    print(f"case {kind}", flush=True)
+    dims = (60000, 2, 1) if kind == "windows" else (64, 64, 64)
+    c = W.smooth_random_case(*dims)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        if kind == "batch":
+            b = cnsf.Batch([c.params] * 32)
+            for j in range(32):
+                b.set_state(j, c.Q0)
+        else:
+            b = cnsf.Lattice(c.params)
+            b.set_state(c.Q0)
+    x = torch.zeros(64, device="cuda")
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        x += 1.0
+        b.step(66, b.MODE_GRAPH) if kind == "batch" else b.step(66)
+        free1 = torch.cuda.mem_get_info()[0]
+        x += 1.0
+    torch.cuda.synchronize()
+    assert free0 - free1 >= b.nbytes // 2
+    g.replay()
+    torch.cuda.synchronize()
+    assert float(x[0]) == 2.0
+    del g
     b.close()

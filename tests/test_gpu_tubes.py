@@ -48,3 +48,31 @@ def test_windows_equal_single_updates(bc, dims, storage, scale):
         assert torch.equal(a.buf, b.buf), n
     a.close()
     b.close()
+
+
+# one window and several, with threads left idle: 245, 253, 252, 253 and 255 of 256 at work
+IDLE = [(7, 5, 7), (23, 11, 1), (40, 9, 1), (60, 11, 1), (700, 5, 3)]
+
+
+@pytest.mark.parametrize("bc", sorted(BCS))
+@pytest.mark.parametrize("dims", IDLE)
+@pytest.mark.parametrize("storage,scale", [(W.STORAGE_FP32, 0.0), (W.STORAGE_FP16, 0.25), (W.STORAGE_BF16, 0.0)])
+def test_windows_with_idle_threads_equal_single_updates(bc, dims, storage, scale):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2608_13437_amd as cnsf
+    prm, Q = _case(dims, bc)
+    prm.update(storage=storage, storage_scale=[scale] * 14, visc_law=W.VISC_POWER, visc_param=0.76)
+    print(f"case {dims} {bc} storage {storage} scale {scale}", flush=True)
+    a, b = cnsf.Lattice(prm), cnsf.Lattice(prm)
+    for L in (a, b):
+        L.set_state(Q)
+    a.set_launch(*a.get_launch())
+    for n in (70, 9, 34, 65):
+        a.step(n)
+        b.step(n)
+        assert a.info()[:2] == b.info()[:2]
+        assert torch.equal(a.buf, b.buf), n
+    a.close()
+    b.close()

@@ -400,3 +400,28 @@ def test_replayed_lattices_capture_anew_after_a_shape_change(host):
     for rep, captures, replays, n, updates, s in r:
         assert captures == (rep in (0, 1, 3)), (rep, captures)
         assert replays >= 1 and updates == 32 * captures + n - 32 * replays, (rep, replays, updates)
+
+
+def test_lattices_of_the_window_tests_run_windows(host):
+    """The bitwise tests of the windows compare them with single updates, not those with themselves."""
+    import test_gpu_tubes as g
+    dims = g.test_windows_equal_single_updates.pytestmark
+    dims = [d for m in dims if m.args and m.args[0] == "dims" for d in m.args[1]]
+    assert len(dims) == 7
+    r = host(f'''
+        out = []
+        for d in {dims + g.IDLE!r}:
+            for bc in range(4):
+                for storage in (0, 1, 2):
+                    L = lattice(box(*d, storage=storage, bc_x=bc, wall_u=[[0.0] * 3] * 2, wall_T=[0.0, 1.1],
+                                    Q_left=[1, 0, 0, 0, 2.5] + [0] * 9, Q_right=[1, 0, 0, 0, 2.5] + [0] * 9))
+                    cnsf.cnsf_step(L, 70)
+                    names = launched()
+                    out.append([list(d), bc, storage, names.count("k_tube"), names.count("k_update")])
+        done(out)
+    ''')
+    for d, bc, storage, windows, updates in r:
+        if d == [50, 5, 7]:
+            assert windows == 0                    # a cross-section too wide: kept as it is in that list
+        else:
+            assert windows > 0 and updates == 0, (d, bc, storage)
