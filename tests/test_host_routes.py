@@ -425,3 +425,17 @@ def test_lattices_of_the_window_tests_run_windows(host):
             assert windows == 0                    # a cross-section too wide: kept as it is in that list
         else:
             assert windows > 0 and updates == 0, (d, bc, storage)
+
+
+def test_lattices_of_the_viscosity_test_run_pairs(host):
+    import test_gpu_pairs as g
+    r = host(f'''
+        out = []
+        for nx, ny, nz, storage, law, param, calls in {g.LAWS!r}:
+            L = lattice(box(nx, ny, nz, storage=storage))
+            for n in calls:
+                cnsf.cnsf_step(L, n)
+            out.append(launched().count("k_pair"))
+        done(out)
+    ''')
+    assert min(r) >= 2, r
