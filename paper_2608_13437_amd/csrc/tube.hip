@@ -151,6 +151,9 @@ k_tube(const typename Store<ST>::T* src, typename Store<ST>::T* dst, const Geom 
     for (int i = 0; i < NV; ++i) {
       float v = f[k][i];
       if (ST != 0 && SC) v *= cd.inv_scale[k];
+      // a value that went through the storage format comes back to its code; fused with the conversion to FP16 the
+      // product gains + 0, and a negative zero (an update's underflow) would lose its sign
+      if (ST == 1 && SC) asm volatile("" : "+v"(v));
       buf_store<ST>(rs, slot_offset<ST>(g, i, cell), v);
     }
   }

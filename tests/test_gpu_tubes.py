@@ -76,3 +76,31 @@ def test_windows_with_idle_threads_equal_single_updates(bc, dims, storage, scale
         assert torch.equal(a.buf, b.buf), n
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("bc", sorted(BCS))
+@pytest.mark.parametrize("scale", [0.25, 0.3])
+@pytest.mark.parametrize("dims", [(16, 4, 4), (90, 4, 3)])
+def test_scaled_codes_keep_the_sign_of_zero(dims, scale, bc):
+    """Updates leave a few negative zeros among scaled FP16 codes (small negative deviations that
+    underflow); a window stores them as it found them."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2608_13437_amd as cnsf
+    prm, Q = _case(dims, bc)
+    prm.update(storage=W.STORAGE_FP16, storage_scale=[scale] * 14)
+    print(f"case {dims} {bc} scale {scale}", flush=True)
+    a, b = cnsf.Lattice(prm), cnsf.Lattice(prm)
+    for L in (a, b):
+        L.set_state(Q)
+    zeros = 0
+    for n in (70, 16, 32, 64):
+        b.step(n)
+        for _ in range(n):
+            a.step(1)
+        zeros += int((a.buf.view(torch.int16) == -32768).sum())
+        assert torch.equal(a.buf, b.buf), n
+    print(f"  {zeros} negative zeros", flush=True)
+    a.close()
+    b.close()
