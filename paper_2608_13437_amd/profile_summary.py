@@ -7,7 +7,8 @@ usage:
   python -m paper_2608_13437_amd.profile_summary requests <dram.csv> <copy_dram.csv> <copy_bytes>
          <storage> <out.json> "<command>"
 The traffic summary scales FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of the
-update by the factor the same counter needs on a plain copy of known size.
+update by the factor the same counter needs on a plain copy of known size, and
+adds up those of the paired passes per pass (two updates).
 The requests summary does the same with the DRAM read and write request
 counts (TCC_EA0_RDREQ_DRAM_sum, TCC_EA0_WRREQ_DRAM_sum), a cross-check of
 the first from another counter.
@@ -20,10 +21,11 @@ import re
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-# the update kernel, its per-cell code, and the population layout and default
-# launch shape it runs with
-SOURCES = ["paper_2608_13437_amd/csrc/update.hip", "paper_2608_13437_amd/csrc/cnsf_impl.h",
-           "paper_2608_13437_amd/csrc/layout.cpp"]
+# every kernel that the profiled programs run, their per-cell code, and the population layout and
+# launch shapes they run with
+SOURCES = ["paper_2608_13437_amd/csrc/" + f for f in (
+    "update.hip", "pair.hip", "tube.hip", "batch.hip", "diag.hip", "lines.hip", "cnsf_impl.h", "diag_common.h", "lines.h",
+    "layout.cpp")]
 
 
 def kernel_hash():
@@ -81,6 +83,9 @@ def stats(path, out, command, bench_log=None):
 # the periodic update without the fused diagnostics: k_update<storage, 0, scaled, parity, false>
 UPDATE = re.compile(r"k_update<\d, 0, (false|true), [01], false>")
 COPY = re.compile(r"k_copy")
+# the launches of a paired pass; a pass through slabs begins with one k_plane_save, any other is one launch
+PAIR = re.compile(r"k_pair<|k_plane_(save|put)<")
+PASS = re.compile(r"k_plane_save<")
 
 
 def counter(path, pattern):
@@ -101,6 +106,13 @@ def traffic(fetch, write, cfetch, cwrite, copy_bytes, storage, out, command):
     rec["copy_factor"] = dict(FETCH_SIZE=round(ffac, 4), WRITE_SIZE=round(wfac, 4))
     rec[storage] = dict(fetch_bytes=[round(x) for x in fb], write_bytes=[round(x) for x in wb],
                         bytes_per_launch=round(sum(per) / len(per)), command=command)
+    pairs = counter(fetch, PAIR), counter(write, PAIR)
+    if pairs[0]:
+        passes = [len(counter(f, PASS)) or len(v) for f, v in zip((fetch, write), pairs)]
+        rec[storage]["paired_pass"] = dict(
+            passes=passes[0], launches=len(pairs[0]),
+            fetch_bytes=round(sum(pairs[0]) * 1024 * ffac / passes[0]),
+            write_bytes=round(sum(pairs[1]) * 1024 * wfac / passes[1]))
     json.dump(rec, open(out, "w"), indent=1)
 
 

@@ -80,3 +80,51 @@ def test_traffic_scales_counters_by_the_copy_calibration(tmp_path):
     assert rec["fp32"]["write_bytes"] == [2_048_000, 2_048_000]
     assert rec["fp32"]["bytes_per_launch"] == pytest.approx((2_048_000 + 2_252_800) / 2 + 2_048_000)
     assert rec["kernel_hash"] == ps.kernel_hash()
+
+
+def test_hash_covers_every_kernel_source(tmp_path, monkeypatch):
+    import os
+    import shutil
+    src = os.path.join(ps.ROOT, "paper_2608_13437_amd", "csrc")
+    dst = tmp_path / "paper_2608_13437_amd" / "csrc"
+    shutil.copytree(src, dst)
+    monkeypatch.setattr(ps, "ROOT", str(tmp_path))
+    seen = {ps.kernel_hash()}
+    kernels = [f for f in os.listdir(dst) if f.endswith(".hip")] + ["cnsf_impl.h", "diag_common.h", "layout.cpp"]
+    for i, f in enumerate(sorted(kernels)):
+        with open(dst / f, "a") as fh:
+            fh.write("// changed\n")
+        seen.add(ps.kernel_hash())
+        assert len(seen) == i + 2, f
+
+
+@pytest.mark.parametrize("slabs", [0, 3])
+def test_traffic_of_paired_passes_is_per_pass(tmp_path, slabs):
+    for c in ("cf", "cw"):
+        write_counters(tmp_path / f"{c}.csv", "cnsf::k_copy(uint4 const*)", [1024.0])
+    names = [UPD.format(st=0, par=0)]
+    vals = [10.0]
+    for _ in range(4):
+        if slabs:
+            names += ["void cnsf::k_plane_save<float>(float const*)"] + ["void cnsf::k_pair<0, false, true>(x)"] * slabs
+            names += ["void cnsf::k_plane_put<float>(float const*)"]
+            vals += [1.0] + [100.0] * slabs + [1.0]
+        else:
+            names += ["void cnsf::k_pair<0, false, false>(x)"]
+            vals += [100.0]
+    names += ["void cnsf::k_pair_batch<0, false>(x)"]
+    vals += [999.0]
+    for f in ("f", "w"):
+        with open(tmp_path / f"{f}.csv", "w", newline="") as fh:
+            w = csv.DictWriter(fh, fieldnames=["Kernel_Name", "Counter_Value"])
+            w.writeheader()
+            for n, v in zip(names, vals):
+                w.writerow(dict(Kernel_Name=n, Counter_Value=v))
+    out = tmp_path / "traffic.json"
+    ps.traffic(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), str(tmp_path / "cf.csv"), str(tmp_path / "cw.csv"),
+               str(1024 * 1024), "fp32", str(out), "cmd")
+    rec = json.load(open(out))["fp32"]
+    per_pass = 1024 * (100 * slabs + 2 if slabs else 100)
+    assert rec["paired_pass"] == dict(passes=4, launches=4 * (slabs + 2 if slabs else 1), fetch_bytes=per_pass,
+                                      write_bytes=per_pass)
+    assert rec["bytes_per_launch"] == 2 * 10 * 1024
