@@ -190,7 +190,8 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * (ny * nz of a few tens of cells at most: tubes, channels, columns) likewise
  * make several updates per launch in calls of 4 to 8 updates and more (by the
  * cross-section); unless they have no more than 256 cells, with a workspace of the
- * array's size, made as above and within the same eighth of the free memory.
+ * array's size, made as above and, beyond 16 MiB, within the same eighth of the free
+ * memory.
  * CNSF_E_DEVICE if a launch is refused; cnsf_get_info then reports the level that
  * the array holds.  Where large lattices are shifted within their array by slabs, a
  * pass refused half way leaves no level there: every call that needs one

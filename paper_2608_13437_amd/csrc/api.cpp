@@ -389,6 +389,9 @@ bool pair_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   return L->pair_wanted;
 }
 
+// Second arrays of windows up to this size are made without a look at the free memory, which takes 5 to 30 us.
+constexpr size_t TUBE_WS_UNASKED = (size_t)16 << 20;
+
 // Whether `L` makes n updates by windows of several (tube.hip); decides and allocates like pair_ready.
 bool tube_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   if (L->own_launch) return false;
@@ -410,7 +413,8 @@ bool tube_ready(cnsf_lattice* L, int64_t n, bool may_alloc) {
   if (L->tube_missed + (capture ? 125.0 : 0.0) < ws_cost(L->bytes)) return false;
   const RelaxedCapture relaxed;
   size_t freeb = 0, total = 0;
-  L->tube_wanted = hipMemGetInfo(&freeb, &total) == hipSuccess && L->bytes <= freeb / 8;
+  if (L->bytes > TUBE_WS_UNASKED)
+    L->tube_wanted = hipMemGetInfo(&freeb, &total) == hipSuccess && L->bytes <= freeb / 8;
   if (L->tube_wanted && hipMalloc(&L->tube_ws, L->bytes) != hipSuccess) {
     L->tube_ws = nullptr;
     L->tube_wanted = false;

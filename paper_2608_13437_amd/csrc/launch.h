@@ -31,11 +31,11 @@ hipError_t launch_moments(int storage, const void* pop, double* out, const Geom&
                           uint32_t cell0, uint32_t nslab, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 
-// What making a workspace costs a call (us; first call with / without: 256 x 4 x 4 FP32, 1.6 MB, 37 / 35; 1024 x 4 x 4,
-// 6.4 MB, 70 / 40; 64^3, 103 MB, 320 / 208; 4.5 GB 1.5 ms).
+// What making a workspace costs a call (us; first call with / without: 256 x 4 x 4 FP32, 1.6 MB, from the runtime's
+// pool, 37 / 35; 1024 x 4 x 4, 6.4 MB, 70 / 40; 64^3, 103 MB, 320 / 208; 4.5 GB 1.5 ms).
 inline double ws_cost(size_t bytes) {
   const double mb = 1e-6 * (double)bytes;
-  return (mb < 24.0 ? 5.0 + 4.0 * mb : 100.0) + 0.3 * mb;
+  return (mb < 2.0 ? 2.0 : mb < 24.0 ? 5.0 + 4.0 * mb : 100.0) + 0.3 * mb;
 }
 
 // Two updates in one pass (pair.hip): planes of the workspace, planes per launch, planes per block,

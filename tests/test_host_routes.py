@@ -224,8 +224,10 @@ def test_workspace_of_windows_is_bounded_and_made_when_it_pays(host):
         out["long_tight"] = held(box(20000000, 1, 1), (4, 40, 400))
         hip.double_memory(8 * GB)
         out["tight"] = held(box(1024, 4, 4), (400,))
-        hip.double_memory(50000000)
-        out["very_tight"] = held(box(1024, 4, 4), (400, 400))
+        for name, prm, room in (("refused", box(60000, 2, 1), 300), ("allowed", box(60000, 2, 1), 600),
+                                ("small", box(8000, 2, 2), 80)):        # 47 MB, 47 MB and 12.5 MB
+            hip.double_memory(room * 1000000)
+            out[name] = held(prm, (400, 400))
         done(out)
     ''')
     for k, v in r.items():
@@ -235,7 +237,9 @@ def test_workspace_of_windows_is_bounded_and_made_when_it_pays(host):
     last = {k: v["calls"][-1][1:] for k, v in r.items()}
     for k in ("long", "short_calls", "graph", "once", "tight"):
         assert last[k] == [r[k]["nb"], True], (k, r[k])
-    for k in ("long_tight", "very_tight"):
+    for k in ("allowed", "small"):
+        assert last[k] == [r[k]["nb"], True], (k, r[k])
+    for k in ("long_tight", "refused"):
         assert last[k] == [0, False], (k, r[k])
     assert last["one_window"] == [0, True]
     assert r["short_calls"]["calls"][0][1:] == [0, False]      # ten updates do not pay for 6.4 MB
