@@ -180,22 +180,24 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * Lattices of at most 2^21 cells replay a HIP graph of 32 updates, captured on
  * first use, when n >= 64 (the results are those of single launches); while the
  * lattice's stream is itself being captured, the updates are plain launches.
- * Periodic lattices for which it is faster (most of 96^3 and more) advance four
- * updates at a time, two per pass over memory, with the same results bit for
- * bit, when n >= 4 (5 from an odd level).  The call with which this would have
- * saved the cost of it (the first one, but for short calls of small lattices)
- * allocates a workspace, kept until cnsf_destroy: the array's size up to 2 GiB (16-bit
- * storage: 8 GiB), beyond that 2 GiB or an eighth of the array, never more than
- * an eighth of the free device memory; without it (or after cnsf_set_launch) the lattice stays on single updates.  Thin lattices
- * (ny * nz of a few tens of cells at most: tubes, channels, columns) likewise
- * make several updates per launch in calls of 4 to 8 updates and more (by the
- * cross-section); unless they have no more than 256 cells, with a workspace of the
- * array's size, made as above and, beyond 16 MiB, within the same eighth of the free
- * memory.
+ * Periodic lattices for which it is faster by a model of measured times advance
+ * four updates at a time, two per pass over memory, with the same results bit for
+ * bit, when n >= 4 (5 from an odd level): FP32 most cubes of 62^3 to 176^3 and larger
+ * ones of edges that are multiples of 4 (from 288^3 of 8 or 16); 16-bit 128^3, 192^3
+ * and most multiples of 16 from 240^3.  The call with which this would have saved
+ * the cost of it (the first one, but for short calls of small lattices) allocates a
+ * workspace, kept until cnsf_destroy: the array's size up to 2 GiB (16-bit storage:
+ * 8 GiB), beyond that 2 GiB or an eighth of the array, never more than an eighth of
+ * the free device memory; without it (or after cnsf_set_launch) the lattice stays on
+ * single updates.  Thin lattices (ny * nz of a few tens of cells at most: tubes,
+ * channels, columns) likewise make several updates per launch in calls of 4 to 8
+ * updates and more (by the cross-section); unless they have no more than 256 cells,
+ * with a workspace of the array's size, made as above and, beyond 16 MiB, within the
+ * same eighth of the free memory.
  * CNSF_E_DEVICE if a launch is refused; cnsf_get_info then reports the level that
  * the array holds.  Where large lattices are shifted within their array by slabs, a
- * pass refused half way leaves no level there: every call that needs one
- * returns CNSF_E_DEVICE until cnsf_set_state (from plane 0) or cnsf_import_populations. */
+ * pass refused half way leaves no level there: every call that needs one returns
+ * CNSF_E_DEVICE until cnsf_set_state (from plane 0) or cnsf_import_populations. */
 int cnsf_step(cnsf_lattice* lat, int64_t n);
 
 /* Time the update on this lattice's population array: one untimed update, then

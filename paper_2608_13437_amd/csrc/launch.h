@@ -120,7 +120,7 @@ hipError_t launch_spectral(const Geom& g, double dx, double* fields, DiagPartial
 hipError_t launch_diag_final(const DiagPartial* partials, int nparts, DiagPartial* tmp, int ntmp,
                              const DiagPartial* second, int nsecond, DiagPartial* out, hipStream_t s);
 // Shell spectrum of the velocity held in fields (u, v, w: the first 3 * ncells
-// doubles, written by launch_diag_sums); uses fields[4 ncells, 7 ncells) as
+// doubles, written by launch_velocity), which it overwrites; uses fields[4 ncells, 8 ncells) as
 // workspace and partial (SHELL_PARTS * nz * spectrum_shells(nx) doubles).  Writes nout
 // values to E (zero beyond the shell count).  Cubic periodic lattices only.
 constexpr uint32_t SHELL_PARTS = 4;

@@ -24,14 +24,15 @@
 // are one block per CU.  Every x-row of a tile also touches the 128-byte lines of its two ring
 // cells, which are whole lines of the neighbouring tiles: they are cheap only while both blocks
 // are at the same plane and the line is in their XCD's L2 (tiles of one XCD are a contiguous
-// patch).  512^3 FP32, array fetched over its size per pass: 32 x 8 tiles 1.99x, 64 x 4 tiles
-// 1.84x, with non-temporal stores, which keep the written planes from pushing those lines out,
-// 1.46x.  The next plane's loads are issued before the second collision: 14.5 -> 13.9 ms per update
+// patch).  Tiles of 64 x 4 fetch less than 32 x 8, and non-temporal stores, which keep the written planes from
+// pushing those lines out, less again: 512^3 FP32 fetches 1.45 times the array per pass (FP16 1.18 times).
+// The next plane's loads are issued before the second collision: 14.5 -> 13.9 ms per update
 // (same array), 16-bit 10.9 -> 8.4.
 // Measured on MI355X per update, single updates -> pairs: 512^3 FP32 17.5 -> 10.9 ms on a fast
-// array, 20.8 -> 13.7 ms on a plain one; FP16 10.5 -> 8.0 ms (plain); 256^3 FP32 2.60 -> 1.50 ms,
-// FP16 1.27 -> 0.96 ms; 128^3 FP32 0.336 -> 0.188 ms.  What bounds it now: FP32 the fetch above,
-// 16-bit the vector units (7 + 4 wave collisions per 256 cells, 4.4 of 7.3 us a plane).
+// array, 20.8 -> 13.7 ms on a plain one; FP16 10.5 -> 8.0 ms (plain); 256^3 FP32 2.61 -> 1.54 ms,
+// FP16 1.28 -> 0.94 ms; 128^3 FP32 0.337 -> 0.194 ms.  What bounds it now: FP32 the fetch above
+// (vector units busy 29% of a pass at 256^3), 16-bit the vector units (58%: 7 + 4 wave collisions per 256
+// cells, three of them on the fullest SIMD).
 #include <algorithm>
 #include <type_traits>
 

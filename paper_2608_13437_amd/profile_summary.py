@@ -6,12 +6,16 @@ usage:
          <copy_write.csv> <copy_bytes> <storage> <out.json> "<commands>"
   python -m paper_2608_13437_amd.profile_summary requests <dram.csv> <copy_dram.csv> <copy_bytes>
          <storage> <out.json> "<command>"
+  python -m paper_2608_13437_amd.profile_summary vector <sq.csv> <storage> <out.json> "<command>"
 The traffic summary scales FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of the
 update by the factor the same counter needs on a plain copy of known size, and
 adds up those of the paired passes per pass (two updates).
 The requests summary does the same with the DRAM read and write request
 counts (TCC_EA0_RDREQ_DRAM_sum, TCC_EA0_WRREQ_DRAM_sum), a cross-check of
 the first from another counter.
+The vector summary gives the share of the SIMDs' time in which they issue vector
+instructions, for the single update and the paired pass (SQ_ACTIVE_INST_VALU counts
+four cycles, GRBM_GUI_ACTIVE the cycles of all 8 XCDs of 128 SIMDs each).
 """
 import csv
 import hashlib
@@ -139,10 +143,24 @@ def requests(dram, cdram, copy_bytes, storage, out, command):
     json.dump(rec, open(out, "w"), indent=1)
 
 
+def vector(sq, storage, out, command):
+    rec = json.load(open(out)) if os.path.exists(out) else {}
+    rec["kernel_hash"] = kernel_hash()
+    rec[storage] = dict(command=command)
+    for name, pattern in (("k_update", UPDATE), ("k_pair", re.compile(r"k_pair<"))):
+        c = _by_counter(sq, pattern)
+        if c:
+            busy = 4 * sum(c["SQ_ACTIVE_INST_VALU"]) / (128 * sum(c["GRBM_GUI_ACTIVE"]))
+            rec[storage][name] = dict(launches=len(c["GRBM_GUI_ACTIVE"]), vector_busy=round(busy, 3))
+    json.dump(rec, open(out, "w"), indent=1)
+
+
 if __name__ == "__main__":
     if sys.argv[1] == "stats":
         stats(*sys.argv[2:6])
     elif sys.argv[1] == "requests":
         requests(*sys.argv[2:8])
+    elif sys.argv[1] == "vector":
+        vector(*sys.argv[2:6])
     else:
         traffic(*sys.argv[2:10])

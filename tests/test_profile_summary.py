@@ -128,3 +128,19 @@ def test_traffic_of_paired_passes_is_per_pass(tmp_path, slabs):
     assert rec["paired_pass"] == dict(passes=4, launches=4 * (slabs + 2 if slabs else 1), fetch_bytes=per_pass,
                                       write_bytes=per_pass)
     assert rec["bytes_per_launch"] == 2 * 10 * 1024
+
+
+def test_vector_share_of_the_simds_time(tmp_path):
+    with open(tmp_path / "sq.csv", "w", newline="") as fh:
+        w = csv.DictWriter(fh, fieldnames=["Kernel_Name", "Counter_Name", "Counter_Value"])
+        w.writeheader()
+        for name, active in ((UPD.format(st=1, par=0), 3200.0), ("void cnsf::k_pair<1, false, false>(x)", 6400.0)):
+            for _ in range(2):
+                w.writerow(dict(Kernel_Name=name, Counter_Name="SQ_ACTIVE_INST_VALU", Counter_Value=active))
+                w.writerow(dict(Kernel_Name=name, Counter_Name="GRBM_GUI_ACTIVE", Counter_Value=400.0))
+    out = tmp_path / "v.json"
+    ps.vector(str(tmp_path / "sq.csv"), "fp16", str(out), "cmd")
+    rec = json.load(open(out))
+    assert rec["kernel_hash"] == ps.kernel_hash()
+    assert rec["fp16"]["k_update"] == dict(launches=2, vector_busy=0.25)
+    assert rec["fp16"]["k_pair"] == dict(launches=2, vector_busy=0.5)
