@@ -190,8 +190,8 @@ int cnsf_set_primitive(cnsf_lattice* lat, const double* P, int32_t z0, int32_t n
  * 8 GiB), beyond that 2 GiB or an eighth of the array, never more than an eighth of
  * the free device memory; without it (or after cnsf_set_launch) the lattice stays on
  * single updates.  Thin lattices (ny * nz of a few tens of cells at most: tubes,
- * channels, columns) likewise make several updates per launch in calls of 4 to 8
- * updates and more (by the cross-section); unless they have no more than 256 cells,
+ * channels, columns) likewise make several updates per launch in calls of 6
+ * updates and more (4 where ny * nz <= 4); unless they have no more than 256 cells,
  * with a workspace of the array's size, made as above and, beyond 16 MiB, within the
  * same eighth of the free memory.
  * CNSF_E_DEVICE if a launch is refused; cnsf_get_info then reports the level that

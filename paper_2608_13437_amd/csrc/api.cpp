@@ -648,7 +648,7 @@ static int step_impl(cnsf_lattice* L, int64_t n, bool may_multi, bool may_alloc)
       --left;
     }
   };
-  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, n - L->parity, may_alloc)) {
+  if (!plain && may_multi && n - L->parity >= PAIR_STEPS && tube_ready(L, n, may_alloc)) {
     even();
     if (e == hipSuccess) e = tube_steps(L, left, &left);
   } else if (!plain && may_multi && n - L->parity >= PAIR_STEPS && pair_ready(L, n, may_alloc)) {

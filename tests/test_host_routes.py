@@ -166,7 +166,7 @@ def test_refused_launch_within_slabs_is_not_passed_over(host):
 
 def test_short_calls_of_windowed_lattices(host):
     """Windows go out to the second array and come back, two launches: calls too short for that
-    to pay are single updates (from the even level on), longer ones windows."""
+    to pay are single updates, longer ones windows from the even level on."""
     r = host('''
         out = {}
         for dims in ((1024, 4, 4), (256, 3, 4), (256, 3, 3), (1024, 4, 2), (300, 2, 2), (1024, 1, 1), (16, 4, 4)):
@@ -188,11 +188,11 @@ def test_short_calls_of_windowed_lattices(host):
                 out["%d %d %d %d" % (*dims, storage)] = seen
         done(out)
     ''')
-    least = {(1024, 4, 4): 8, (256, 3, 4): 8, (256, 3, 3): 6, (1024, 4, 2): 6, (300, 2, 2): 4, (1024, 1, 1): 4, (16, 4, 4): 4}
+    least = {(1024, 4, 4): 6, (256, 3, 4): 6, (256, 3, 3): 6, (1024, 4, 2): 6, (300, 2, 2): 4, (1024, 1, 1): 4, (16, 4, 4): 4}
     for key, seen in r.items():
         dims = tuple(int(v) for v in key.split()[:3])
         for n, odd, ran in seen:
-            assert ("k_tube" in ran) == (n >= least[dims]), (key, n, odd, ran)
+            assert ("k_tube" in ran) == (n + odd >= least[dims]), (key, n, odd, ran)
             if "k_tube" in ran:
                 assert ran.count("k_update") == odd + n % 2 and ran.count("k_tube") == (1 if dims[0] == 16 else 2)
             else:
