@@ -31,9 +31,10 @@ Launch default_launch(int storage) {
 // that the 256 MB last-level cache holds do not want the order of the large ones: 256-cell tiles in spans
 // (512-cell tiles in hardware order / in spans / 256-cell tiles: 48^3 10.8 / 10.2 / 8.6, 56^3 15.6 / 14.4 / 13.2,
 // 80^3 37.0 / 35.3 / 34.3, 100^3 71.2 / 68.6 / 63.0, but 128^3 163 against 179), except where 256-cell tiles
-// would be three to four blocks per CU: the fullest CU has the same cells then, and half the blocks to start (58^3, 2.98 blocks per CU, 17.1 / 15.4 / 15.0; 59^3 17.7 / 16.5 / 16.6; 60^3 17.9 / 17.2 / 17.2; 61^3
-// 18.4 / 17.2 / 17.1; 62^3 19.0 / 18.1 / 18.5; 63^3 19.6 / 19.0 / 19.2; 64^3, 4.0, 18.6 / 18.5 / 19.1; 65^3, 4.2, 24.3 / 23.7
-// / 21.7; 66^3 24.6 / 24.0 / 22.0; 68^3 25.3 / 24.7 / 23.1).
+// would be three to four blocks per CU: the fullest CU has the same cells then, and half the blocks to start
+// (58^3, 2.98 blocks per CU, 17.1 / 15.4 / 15.0; 59^3 17.7 / 16.5 / 16.6; 60^3 17.9 / 17.2 / 17.2; 61^3 18.4 / 17.2 /
+// 17.1; 62^3 19.0 / 18.1 / 18.5; 63^3 19.6 / 19.0 / 19.2; 64^3, 4.0, 18.6 / 18.5 / 19.1; 65^3, 4.2, 24.3 / 23.7 / 21.7;
+// 66^3 24.6 / 24.0 / 22.0; 68^3 25.3 / 24.7 / 23.1).
 Launch lattice_launch(int storage, uint64_t ncells, int cus) {
   Launch lc = default_launch(storage);
   if (ncells <= 96 * 1024) {

@@ -174,10 +174,11 @@ bool tube_plan(const Geom& g, int storage, int cus, TubePlan* out) {
     return true;
   }
   const bool fp32 = storage == 0;
-  // Short calls: windows go out and come back, two launches (us per call among others, windows / single, the worst of
-  // FP32 and 16-bit, walls and periodic): 4 updates of 1024 x 1 x 1 18.8 / 20.2, 3000 x 2 x 2 22.8 / 22.0, but 1024 x 4 x 2
-  // 23.5 / 19.9 and 1024 x 4 x 4 32.4 / 22.3.  From 6 on the queue tells: 1024 x 4 x 4 36.7 / 33.2 among others, but with a
-  // readout after it, as most calls of a few updates have, 101 / 143 (64 x 4 x 4 58 / 110; 4 updates 54 / 54).
+  // Short calls: windows go out and come back, two launches (us per call among others, windows / single, the
+  // worst of FP32 and 16-bit, walls and periodic): 4 updates of 1024 x 1 x 1 18.8 / 20.2, 3000 x 2 x 2 22.8 / 22.0,
+  // but 1024 x 4 x 2 23.5 / 19.9 and 1024 x 4 x 4 32.4 / 22.3.  From 6 on the queue tells: 1024 x 4 x 4 36.7 / 33.2
+  // among others, but with a readout after it, as most calls of a few updates have, 101 / 143 (64 x 4 x 4
+  // 58 / 110; 4 updates 54 / 54).
   const int least = most >= 64 ? 4 : 6;
   const double cell_mb = NP * (fp32 ? 4e-6 : 2e-6);
   double best = 1e300;
