@@ -25,7 +25,8 @@
 // cells, which are whole lines of the neighbouring tiles: they are cheap only while both blocks
 // are at the same plane and the line is in their XCD's L2 (tiles of one XCD are a contiguous
 // patch).  Tiles of 64 x 4 fetch less than 32 x 8, and non-temporal stores, which keep the written planes from
-// pushing those lines out, less again: 512^3 FP32 fetches 1.45 times the array per pass (FP16 1.18 times).
+// pushing those lines out, less again: 512^3 FP32 fetches 1.45 to 1.61 times the array per pass (by the
+// allocation; FP16 1.18 times).
 // The next plane's loads are issued before the second collision: 14.5 -> 13.9 ms per update
 // (same array), 16-bit 10.9 -> 8.4.
 // Measured on MI355X per update, single updates -> pairs: 512^3 FP32 17.5 -> 10.9 ms on a fast
